@@ -97,6 +97,17 @@ __device__ __forceinline__ void copy_to_lds16(const void* g, uint32_t lds) {
       : "memory", "m0");
 }
 
+// The same with 4 bytes per lane (256 bytes per wave instruction).
+__device__ __forceinline__ void copy_to_lds4(const void* g, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %0, off"
+      :
+      : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds))
+      : "memory", "m0");
+}
+
 // The same copy from sbase + voff: sbase wave-uniform (scalar registers),
 // voff a 32-bit byte offset per lane.
 __device__ __forceinline__ void copy_to_lds16_at(const void* sbase, uint32_t voff, uint32_t lds) {
@@ -141,6 +152,53 @@ __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// A row's LayerNorm factors (rstd, -mean rstd) from its `parts` equal-width
+// statistics partials (mean, biased variance), part(p): the row's mean is
+// the average of the partial means, its variance the average partial
+// variance plus the variance of the partial means.
+//
+// With MAXP > 0 (parts <= MAXP) every partial is loaded before any is used,
+// so the loads' latencies overlap; MAXP = 0 takes any count.  Both forms sum
+// in the same order.
+template <int MAXP, class Part>
+__device__ __forceinline__ float2 ln_row_factors(Part part, int parts, float eps) {
+  float sm = 0.0f, sv = 0.0f, sd = 0.0f;
+  const float inv_p = 1.0f / (float)parts;
+  float mu;
+  if constexpr (MAXP > 0) {
+    float2 v[MAXP];
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p)
+      if (p < parts) v[p] = part(p);
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p)
+      if (p < parts) {
+        sm += v[p].x;
+        sv += v[p].y;
+      }
+    mu = sm * inv_p;
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p)
+      if (p < parts) {
+        const float dm = v[p].x - mu;
+        sd = fmaf(dm, dm, sd);
+      }
+  } else {
+    for (int p = 0; p < parts; ++p) {
+      const float2 v = part(p);
+      sm += v.x;
+      sv += v.y;
+    }
+    mu = sm * inv_p;
+    for (int p = 0; p < parts; ++p) {
+      const float dm = part(p).x - mu;
+      sd = fmaf(dm, dm, sd);
+    }
+  }
+  const float rstd = 1.0f / sqrtf(fmaf(sv + sd, inv_p, eps));
+  return make_float2(rstd, -mu * rstd);
 }
 
 // GELU, z Phi(z) = 0.5 z (1 + erf(z / sqrt 2)), with erf by Abramowitz &

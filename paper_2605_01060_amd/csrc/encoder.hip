@@ -215,45 +215,54 @@ surge_status encode_chunks(surge_encoder* e, int64_t n_texts, const int32_t* d_t
     // hold raw (pre-LN) residual rows, SX and SY their statistics partials
     // (written by the residual GEMMs), RX and RY the per-row factors.
     const int parts = d / linear_stats_width(T, d);  // partials of a [T, d] output
+    // In a small chunk the GEMMs merge the partials themselves (QKV and
+    // O-projection those of X, FFN1 and FFN2 those of Y) and the row-factor
+    // kernel does not run, but for the pooling after the last layer.
+    const bool merge_x = linear_merges_stats(T, 3 * d, parts, e->n_cus) &&
+                         linear_merges_stats(T, d, parts, e->n_cus);
+    const bool merge_y = linear_merges_stats(T, f, parts, e->n_cus) &&
+                         linear_merges_stats(T, d, parts, e->n_cus);
+    LinearExtra from_x, from_y;  // where the factors of X's and Y's rows come from
+    from_x.n_cus = from_y.n_cus = e->n_cus;
+    from_x.rows_in = merge_x ? nullptr : e->RX;
+    from_y.rows_in = merge_y ? nullptr : e->RY;
+    from_x.stats_in = e->SX;
+    from_y.stats_in = e->SY;
+    from_x.parts_in = from_y.parts_in = parts;
+    from_x.eps = from_y.eps = D.ln_eps;
     for (int l = 0; l < D.n_layers; ++l) {
       const LayerWeights& w = e->layers[l];
       const LayerWeights* pw = l > 0 ? &e->layers[l - 1] : nullptr;
-      LinearExtra xq;  // QKV: LN2 of the previous layer folded in (layer 0: plain)
-      xq.n_cus = e->n_cus;
-      xq.rows_in = e->RX;
+      LinearExtra xq = from_x;  // QKV: LN2 of the previous layer folded in (layer 0: plain)
       xq.col_s = w.sqkv;
       LAUNCH(SURGE_KERNEL_QKV, 2.0 * Td * d * 3 * d, 2.0 * (Td * d + 3.0 * d * d + Td * 3 * d),
              launch_linear(e->X, w.wqkv, w.bqkv, nullptr, e->QKV, T, 3 * d, d,
                            l == 0 ? EPI_BIAS : EPI_FOLD, xq, stream));
       LAUNCH(SURGE_KERNEL_ATTN, 4.0 * d * sumL2, 2.0 * Td * 4 * d,
              launch_attention(e->QKV, e->CTX, e->d_cu, e->d_items, n_items, D.n_heads, dh, stream));
-      LinearExtra xo;  // O-proj + residual (LN2 of the previous layer applied to it)
-      xo.n_cus = e->n_cus;
-      xo.rows_in = e->RX;
+      LinearExtra xo = from_x;  // O-proj + residual (LN2 of the previous layer applied to it)
       xo.stats_out = e->SY;
       xo.gamma = pw ? pw->ln2g : nullptr;
       xo.beta = pw ? pw->ln2b : nullptr;
       LAUNCH(SURGE_KERNEL_OPROJ, 2.0 * Td * d * d, 2.0 * (3.0 * Td * d + (double)d * d),
              launch_linear(e->CTX, w.wo, w.bo, e->X, e->Y, T, d, d,
                            l == 0 ? EPI_RES_STATS : EPI_LNRES_STATS, xo, stream));
-      LAUNCH(SURGE_KERNEL_LN1, 0.0, Td * (8.0 * parts + 8.0),
-             launch_ln_rows(e->SY, parts, T, D.ln_eps, e->RY, stream));
-      LinearExtra x1;  // FFN1: LN1 folded in
-      x1.n_cus = e->n_cus;
-      x1.rows_in = e->RY;
+      if (!merge_y)
+        LAUNCH(SURGE_KERNEL_LN1, 0.0, Td * (8.0 * parts + 8.0),
+               launch_ln_rows(e->SY, parts, T, D.ln_eps, e->RY, stream));
+      LinearExtra x1 = from_y;  // FFN1: LN1 folded in
       x1.col_s = w.s1;
       LAUNCH(SURGE_KERNEL_FFN1, 2.0 * Td * d * f, 2.0 * (Td * d + (double)d * f + Td * f),
              launch_linear(e->Y, w.w1, w.b1, nullptr, e->H, T, f, d, EPI_FOLD_GELU, x1, stream));
-      LinearExtra x2;  // FFN2 + residual LN1(Y)
-      x2.n_cus = e->n_cus;
-      x2.rows_in = e->RY;
+      LinearExtra x2 = from_y;  // FFN2 + residual LN1(Y)
       x2.stats_out = e->SX;
       x2.gamma = w.ln1g;
       x2.beta = w.ln1b;
       LAUNCH(SURGE_KERNEL_FFN2, 2.0 * Td * d * f, 2.0 * (Td * f + (double)d * f + 2.0 * Td * d),
              launch_linear(e->H, w.w2, w.b2, e->Y, e->X, T, d, f, EPI_LNRES_STATS, x2, stream));
-      LAUNCH(SURGE_KERNEL_LN2, 0.0, Td * (8.0 * parts + 8.0),
-             launch_ln_rows(e->SX, parts, T, D.ln_eps, e->RX, stream));
+      if (!merge_x || l == D.n_layers - 1)
+        LAUNCH(SURGE_KERNEL_LN2, 0.0, Td * (8.0 * parts + 8.0),
+               launch_ln_rows(e->SX, parts, T, D.ln_eps, e->RX, stream));
     }
     // The last layer's LN2 is applied inside the pooling.
     const LayerWeights& wl = e->layers[D.n_layers - 1];

@@ -55,10 +55,20 @@ struct LinearExtra {
   const float* gamma = nullptr;      // [N] (LNRES)
   const float* beta = nullptr;       // [N] (LNRES)
   int n_cus = 0;                     // compute units of the device (0: query it)
+  // Where linear_merges_stats says so, rows_in may be NULL and the factors
+  // are merged from the statistics partials by the tiles that need them.
+  const float2* stats_in = nullptr;
+  int parts_in = 0;
+  float eps = 0.0f;
 };
+constexpr int RING_MAX_PARTS = 16;  // most partials per row that a tile merges
 hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias, const uint16_t* R,
                          uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& ex,
                          hipStream_t stream);
+// Whether an [M, N] linear layer can merge its input's (or residual's) row
+// statistics, `parts` partials a row, by itself (ex.stats_in), so that
+// launch_ln_rows need not run before it.  n_cus as in LinearExtra.
+bool linear_merges_stats(int64_t M, int N, int parts, int n_cus);
 // Features per statistics partial written by launch_linear for an [M, N]
 // output (the width of one wave's slice of a tile).
 int linear_stats_width(int64_t M, int N);

@@ -55,13 +55,10 @@
 // other texts share its SuperBatch or chunk, nor on the tile configuration.
 #include <algorithm>
 
-#include "device_common.h"
-#include "kernels.h"
+#include "linear_common.h"
 
 namespace surge {
 namespace {
-
-constexpr int STATS_WIDTH = 64;  // features per row-statistics partial
 
 // Wait until at most `later` stages' copies (CPS instructions each) issued
 // after the one needed next are still in flight.  The vector memory counter
@@ -119,57 +116,6 @@ __device__ __forceinline__ void tile_coords(int b, int n_tiles, int tiles_n, int
 // bank geometry, and an aligned 16-byte pair {2k, 2k+1} stays together
 // (halves swapped when rsw(r) is odd).
 __device__ __forceinline__ int rsw(int r) { return (r & 15) ^ ((r >> 4) & 1); }
-
-// Finishes four consecutive features of one output row and rounds them to
-// bf16: bias (or the folded LayerNorm rs * a + (nm * s + b)), GELU, then
-// the residual `res` (LayerNorm-applied as (r rs + nm) g + beta in the
-// LNRES mode).
-template <int EPI>
-__device__ __forceinline__ uint2 finish4(const float (&a)[4], float4 bb, float4 cs, float4 gg,
-                                         float4 be, float rs, float nm, uint2 res) {
-  constexpr bool FOLD = EPI == EPI_FOLD || EPI == EPI_FOLD_GELU;
-  constexpr bool GELU = EPI == EPI_BIAS_GELU || EPI == EPI_FOLD_GELU;
-  constexpr bool RES = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_RES_STATS || EPI == EPI_LNRES_STATS;
-  constexpr bool LNRES = EPI == EPI_LNRES_STATS;
-  float o0, o1, o2, o3;
-  if constexpr (FOLD) {
-    o0 = fmaf(rs, a[0], fmaf(nm, cs.x, bb.x));
-    o1 = fmaf(rs, a[1], fmaf(nm, cs.y, bb.y));
-    o2 = fmaf(rs, a[2], fmaf(nm, cs.z, bb.z));
-    o3 = fmaf(rs, a[3], fmaf(nm, cs.w, bb.w));
-  } else {
-    o0 = a[0] + bb.x;
-    o1 = a[1] + bb.y;
-    o2 = a[2] + bb.z;
-    o3 = a[3] + bb.w;
-  }
-  if constexpr (GELU) {
-    o0 = gelu_erf(o0);
-    o1 = gelu_erf(o1);
-    o2 = gelu_erf(o2);
-    o3 = gelu_erf(o3);
-  }
-  if constexpr (RES) {
-    float r0 = __uint_as_float(res.x << 16);
-    float r1 = __uint_as_float(res.x & 0xffff0000u);
-    float r2 = __uint_as_float(res.y << 16);
-    float r3 = __uint_as_float(res.y & 0xffff0000u);
-    if constexpr (LNRES) {
-      r0 = fmaf(fmaf(r0, rs, nm), gg.x, be.x);
-      r1 = fmaf(fmaf(r1, rs, nm), gg.y, be.y);
-      r2 = fmaf(fmaf(r2, rs, nm), gg.z, be.z);
-      r3 = fmaf(fmaf(r3, rs, nm), gg.w, be.w);
-    }
-    o0 += r0;
-    o1 += r1;
-    o2 += r2;
-    o3 += r3;
-  }
-  uint2 out;
-  out.x = pack_bf16x2(o0, o1);
-  out.y = pack_bf16x2(o2, o3);
-  return out;
-}
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int EPI, int ORDER>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -425,7 +371,6 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
           EPI == EPI_BIAS_RESIDUAL || EPI == EPI_RES_STATS || EPI == EPI_LNRES_STATS;
       constexpr bool LNRES = EPI == EPI_LNRES_STATS;
       constexpr bool STATS = EPI == EPI_RES_STATS || EPI == EPI_LNRES_STATS;
-      constexpr int PW = STATS_WIDTH;
       constexpr int NP = TM * (TN / 2);  // passes
       // Region row r lives in this wave's X copy slot r/8 of the buffer the
       // last stage released (8 rows of 128 bytes per 1 KB slot).
@@ -487,12 +432,7 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
                                 acc[i][j][4 * g + 3]};
             const uint2 out = finish4<EPI>(a, bb, cs, gg, be, rs, nm, RES ? cell : uint2{0u, 0u});
             cell = out;
-            if constexpr (STATS) {
-              const float v0 = __uint_as_float(out.x << 16), v1 = __uint_as_float(out.x & 0xffff0000u);
-              const float v2 = __uint_as_float(out.y << 16), v3 = __uint_as_float(out.y & 0xffff0000u);
-              st_s += (v0 + v1) + (v2 + v3);
-              st_q = fmaf(v0, v0, fmaf(v1, v1, fmaf(v2, v2, fmaf(v3, v3, st_q))));
-            }
+            if constexpr (STATS) row_stats_add(out, st_s, st_q);
           }
         }
         if constexpr (STATS) {
@@ -501,12 +441,9 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
           const float s1 = st_s + __shfl_xor(st_s, 32, 64);
           const float q1 = st_q + __shfl_xor(st_q, 32, 64);
           const int m = m0 + wm0 + j * 32 + l32;
-          if (lhi == 0 && m < M) {
-            constexpr float inv_w = 1.0f / (float)PW;
-            const float mean = s1 * inv_w;
-            ex.stats_out[(size_t)((n0 + wn0) / PW + ip) * M + m] =
-                make_float2(mean, fmaxf(q1 * inv_w - mean * mean, 0.0f));
-          }
+          if (lhi == 0 && m < M)
+            ex.stats_out[(size_t)((n0 + wn0) / STATS_WIDTH + ip) * M + m] =
+                row_stats_finish(s1, q1);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // region written by all lanes
         u32x4 ov[4];
@@ -543,18 +480,10 @@ hipError_t launch_tiles(const uint16_t* X, const uint16_t* W, const float* bias,
                         uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& ex,
                         hipStream_t stream) {
   if ((int64_t)BM * K * 2 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;  // copy offsets
-  int cus = ex.n_cus;
-  if (cus <= 0) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-  }
   const int tiles_n = N / BN;
   const int64_t tiles_m = (M + BM - 1) / BM;
   const int n_tiles = (int)(tiles_m * tiles_n);
-  const dim3 grid((unsigned)std::min<int64_t>(n_tiles, (int64_t)cus * PER_CU));
+  const dim3 grid((unsigned)std::min<int64_t>(n_tiles, (int64_t)ex.n_cus * PER_CU));
   const dim3 block(WAVES_M * WAVES_N * 64);
 #define SURGE_LAUNCH_EPI(E, O)                                                                   \
   hipLaunchKernelGGL((linear_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, E, O>), grid, block, 0, stream, \
@@ -580,12 +509,49 @@ hipError_t launch_tiles(const uint16_t* X, const uint16_t* W, const float* bias,
 // tiles (4 waves of 64 x 64, two workgroups per CU) otherwise.
 static bool big_tiles(int64_t M, int N) { return N % 256 == 0 && M >= 8192; }
 
+// Below that, where a tile's own chain of latencies is the launch's time:
+// the smallest tile of which there is still at most one per CU.  A smaller
+// tile is a shorter chain (copies, barrier and MFMAs per stage) and spreads
+// the stream of W over more CUs; once there is more than one per CU the
+// shared operand traffic costs more than it saves.  Measured (us per layer,
+// K = 3072, N = 768; 32x64 / 64x64 / 64x128 / 128x128 persistent tiles):
+//   M = 24    8.4 / 10.7 / 16.4 / 25.5     M = 512   9.6 / 11.9 / 20.3 / 27.2
+//   M = 1024  19.5 / 13.2 / 22.1 / 35.1    M = 2080  38.3 / 28.8 / 25.3 / 33.7
+//   M = 4096  58.9 / 48.6 / 47.5 / 34.3.
+static RingTile ring_tile(int64_t M, int N, int n_cus) {
+  auto fits = [&](int bm, int bn) { return (M + bm - 1) / bm * (N / bn) <= n_cus; };
+  if (fits(32, 64)) return RING_32x64;
+  if (fits(64, 64)) return RING_64x64;
+  if (fits(64, 128)) return RING_64x128;
+  return RING_NONE;
+}
+
 int linear_stats_width(int64_t, int) { return STATS_WIDTH; }
 
+// Compute units of the current device, unless the caller knows them.
+static hipError_t resolve_cus(int* n_cus) {
+  if (*n_cus > 0) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return hipDeviceGetAttribute(n_cus, hipDeviceAttributeMultiprocessorCount, dev);
+}
+
+bool linear_merges_stats(int64_t M, int N, int parts, int n_cus) {
+  return parts <= RING_MAX_PARTS && resolve_cus(&n_cus) == hipSuccess &&
+         ring_tile(M, N, n_cus) != RING_NONE;
+}
+
 hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias, const uint16_t* R,
-                         uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& ex,
+                         uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& extra,
                          hipStream_t stream) {
   if (M <= 0) return hipSuccess;
+  LinearExtra ex = extra;
+  hipError_t e = resolve_cus(&ex.n_cus);
+  if (e != hipSuccess) return e;
+  const RingTile tile = ring_tile(M, N, ex.n_cus);
+  if (tile != RING_NONE)
+    return launch_linear_ring(tile, X, W, bias, R, Y, M, N, K, epi, ex, stream);
   if (big_tiles(M, N))
     return launch_tiles<256, 256, 64, 4, 2, 1>(X, W, bias, R, Y, M, N, K, epi, ex, stream);
   return launch_tiles<128, 128, 64, 2, 2, 2>(X, W, bias, R, Y, M, N, K, epi, ex, stream);

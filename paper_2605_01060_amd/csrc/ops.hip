@@ -145,12 +145,12 @@ surge_status surge_op_linear(int64_t M, int32_t N, int32_t K, const uint16_t* d_
 namespace {
 
 // Argument check shared by surge_op_linear_ln and its no-allocation variant;
-// *rows is set when the epilogue reads per-row LayerNorm factors.
+// *factors is set when the epilogue reads per-row LayerNorm factors.
 surge_status check_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* d_x,
                              const uint16_t* d_w, const float* d_bias, const uint16_t* d_res,
                              int32_t epilogue, const float* d_stats_in, int32_t parts_in,
                              const float* d_col_s, const float* d_gamma, const float* d_beta,
-                             float eps, float* d_stats_out, uint16_t* d_y, bool* rows) {
+                             float eps, float* d_stats_out, uint16_t* d_y, bool* factors) {
   if (M < 1 || M > (int64_t)INT32_MAX) return fail(SURGE_ERR_INVALID_ARGUMENT, "M=%lld", (long long)M);
   if (N < 128 || N % 128) return fail(SURGE_ERR_INVALID_ARGUMENT, "N=%d not a multiple of 128", N);
   if (K < 64 || K % 64) return fail(SURGE_ERR_INVALID_ARGUMENT, "K=%d not a multiple of 64", K);
@@ -173,11 +173,12 @@ surge_status check_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* d_
       (d_gamma && !aligned16(d_gamma)) || (d_beta && !aligned16(d_beta)) ||
       (d_stats_in && ((uintptr_t)d_stats_in & 7u)) || (d_stats_out && ((uintptr_t)d_stats_out & 7u)))
     return fail(SURGE_ERR_INVALID_ARGUMENT, "device buffers must be aligned (16 B; stats 8 B)");
-  *rows = fold || lnres;
+  *factors = fold || lnres;
   return SURGE_OK;
 }
 
-// Enqueue the row factors (when `rows` is not NULL) and the linear layer.
+// Enqueue the row factors (when `rows` is not NULL) and the linear layer,
+// which merges the partials itself otherwise (linear_merges_stats).
 surge_status enqueue_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* d_x,
                                const uint16_t* d_w, const float* d_bias, const uint16_t* d_res,
                                int32_t epilogue, const float* d_stats_in, int32_t parts_in,
@@ -189,6 +190,9 @@ surge_status enqueue_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* 
   ex.col_s = d_col_s;
   ex.gamma = d_gamma;
   ex.beta = d_beta;
+  ex.stats_in = (const float2*)d_stats_in;
+  ex.parts_in = parts_in;
+  ex.eps = eps;
   if (rows) {
     HIP_TRY(launch_ln_rows((const float2*)d_stats_in, parts_in, M, eps, rows, s));
     ex.rows_in = rows;
@@ -207,14 +211,14 @@ surge_status surge_op_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t*
                                 const float* d_col_s, const float* d_gamma, const float* d_beta,
                                 float eps, float* d_stats_out, uint16_t* d_y, void* hip_stream) {
   clear_error();
-  bool need_rows = false;
+  bool factors = false;
   surge_status st = check_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in,
                                     parts_in, d_col_s, d_gamma, d_beta, eps, d_stats_out, d_y,
-                                    &need_rows);
+                                    &factors);
   if (st != SURGE_OK) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   DeviceCu rows;  // per-row LayerNorm factors, freed on return
-  if (need_rows) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
+  if (factors && !linear_merges_stats(M, N, parts_in, 0)) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
   st = enqueue_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in, parts_in, d_col_s,
                          d_gamma, d_beta, eps, d_stats_out, d_y, (float2*)rows.ptr, s);
   if (st != SURGE_OK) return st;
@@ -230,16 +234,16 @@ surge_status surge_op_linear_ln_noalloc(int64_t M, int32_t N, int32_t K, const u
                                         const float* d_beta, float eps, float* d_stats_out,
                                         uint16_t* d_y, void* hip_stream) {
   clear_error();
-  bool need_rows = false;
+  bool factors = false;
   surge_status st = check_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in,
                                     parts_in, d_col_s, d_gamma, d_beta, eps, d_stats_out, d_y,
-                                    &need_rows);
+                                    &factors);
   if (st != SURGE_OK) return st;
   float2* rows = nullptr;
-  if (need_rows) {
-    if (M > kScratchRows)
-      return fail(SURGE_ERR_CAPACITY, "M=%lld rows exceed the %lld rows of the static scratch",
-                  (long long)M, (long long)kScratchRows);
+  if (factors && M > kScratchRows)
+    return fail(SURGE_ERR_CAPACITY, "M=%lld rows exceed the %lld rows of the static scratch",
+                (long long)M, (long long)kScratchRows);
+  if (factors && !linear_merges_stats(M, N, parts_in, 0)) {
     st = scratch_address(&rows);
     if (st != SURGE_OK) return st;
   }

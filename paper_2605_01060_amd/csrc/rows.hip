@@ -204,55 +204,16 @@ __global__ __launch_bounds__(256) void pool_l2_scatter_kernel(const uint16_t* __
 }
 
 // Per-row LayerNorm factors from equal-width statistics partials (mean,
-// biased variance) at stats[p * M + row]: the row's mean is the average of
-// the partial means and its variance the average partial variance plus the
-// variance of the partial means.  rows[row] = (rstd, -mean * rstd), so that
-// LN(v) = gamma (v rstd - mean rstd) + beta.  With MAXP > 0 (parts <= MAXP,
-// the encoder's case: d_model / 64 <= 16) every partial is loaded before any
-// is used, so the loads' latencies overlap; MAXP = 0 takes any count.  Both
-// forms sum in the same order.
+// biased variance) at stats[p * M + row]: rows[row] = (rstd, -mean * rstd),
+// so that LN(v) = gamma (v rstd - mean rstd) + beta.  MAXP = 16 is the
+// encoder's case (d_model / 64 <= 16 partials), MAXP = 0 takes any count.
 template <int MAXP>
 __global__ __launch_bounds__(256) void ln_rows_kernel(const float2* __restrict__ stats, int parts,
                                                       int64_t M, float eps,
                                                       float2* __restrict__ rows) {
   const int64_t m = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (m >= M) return;
-  float sm = 0.0f, sv = 0.0f, sd = 0.0f;
-  const float inv_p = 1.0f / (float)parts;
-  if constexpr (MAXP > 0) {
-    float2 v[MAXP];
-#pragma unroll
-    for (int p = 0; p < MAXP; ++p)
-      if (p < parts) v[p] = stats[(size_t)p * M + m];
-#pragma unroll
-    for (int p = 0; p < MAXP; ++p)
-      if (p < parts) {
-        sm += v[p].x;
-        sv += v[p].y;
-      }
-    const float mu = sm * inv_p;
-#pragma unroll
-    for (int p = 0; p < MAXP; ++p)
-      if (p < parts) {
-        const float dm = v[p].x - mu;
-        sd = fmaf(dm, dm, sd);
-      }
-    const float rstd = 1.0f / sqrtf((sv + sd) * inv_p + eps);
-    rows[m] = make_float2(rstd, -mu * rstd);
-  } else {
-    for (int p = 0; p < parts; ++p) {
-      const float2 v = stats[(size_t)p * M + m];
-      sm += v.x;
-      sv += v.y;
-    }
-    const float mu = sm * inv_p;
-    for (int p = 0; p < parts; ++p) {
-      const float dm = stats[(size_t)p * M + m].x - mu;
-      sd = fmaf(dm, dm, sd);
-    }
-    const float rstd = 1.0f / sqrtf((sv + sd) * inv_p + eps);
-    rows[m] = make_float2(rstd, -mu * rstd);
-  }
+  rows[m] = ln_row_factors<MAXP>([&](int p) { return stats[(size_t)p * M + m]; }, parts, eps);
 }
 
 }  // namespace

@@ -375,3 +375,41 @@ def test_pool_l2(d):
     for i in range(len(lengths)):
         ref = E.mean_pool_l2(x64[cu[i]:cu[i + 1]])
         assert np.max(np.abs(got[i] - ref)) < 2e-6, i
+
+
+@pytest.mark.parametrize("N,K", [(384, 64), (384, 320), (1152, 384), (384, 1536)])
+@pytest.mark.parametrize("epi", range(7))
+def test_small_calls_match_the_large_call_bit_for_bit(N, K, epi):
+    """The first M rows of a large call against a call of M rows: M at the
+    edges of the 32- and 64-row tiles and on both sides of the sizes where
+    the tile changes, odd and even numbers of K halves.  Every tile takes the
+    same MFMAs in the same order, so outputs and statistics are equal."""
+    torch = torch_cuda()
+    g = torch.Generator(device="cuda").manual_seed(N + K + epi)
+    m = 128 * (512 // (N // 128) + 1) + 5  # past every one-tile-per-CU size
+
+    def randn(*dims):
+        return torch.randn(dims, generator=g, device="cuda")
+
+    x, w, b = randn(m, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
+    res = randn(m, N).bfloat16() if epi in (2, 5, 6) else None
+    raw = (res if epi == 6 else x).float().view(m, -1, 64)
+    st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)  # [m, parts, 2]
+    parts = st_in.shape[1]
+    vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N)) if epi >= 3 else (None,) * 3
+
+    def call(rows):
+        y = torch.full((rows, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        st = torch.zeros((N // 64, rows, 2), device="cuda")
+        S.surge_op_linear_ln(rows, N, K, x, w, b, res, epi,
+                             st_in[:rows].transpose(0, 1).contiguous(), parts, *vecs, 1e-12, st, y)
+        return y, st
+
+    y, st = call(m)
+    assert not torch.isnan(y).any()
+    tiles64, tiles128 = 256 // (N // 64) * 64, 256 // (N // 128) * 64
+    for rows in (1, 31, 32, 33, 64, 65, tiles64 // 2, tiles64 // 2 + 1, tiles64, tiles64 + 1,
+                 tiles128, tiles128 + 1):
+        ys, ss = call(rows)
+        assert torch.equal(ys, y[:rows]), rows
+        assert torch.equal(ss, st[:, :rows]), rows
