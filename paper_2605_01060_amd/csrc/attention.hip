@@ -5,12 +5,12 @@
 // query attends to the keys of its own text only, bidirectionally, with
 // scale 1/sqrt(dh).
 //
-// Work decomposition.  A work item is (text, 32-query block); the host
+// Work decomposition.  A work item is a 32-query block of a text; the host
 // lists the items of a chunk longest text first, so the long texts start
 // early and the short ones fill in behind them.  A unit is one item for one
-// head (or head pair, below); a wave (a workgroup of its own) handles UNITS_PER_WAVE units,
-// grid-strided, walking each unit's keys in 32-key blocks with an online
-// softmax.
+// head (or head pair, below); a wave (a workgroup of its own) handles 1 to
+// MAX_UNITS_PER_WAVE units, grid-strided, walking each unit's keys in 32-key
+// blocks with an online softmax.
 //
 // Pipelining.  The wave's key blocks form one sequence across its units:
 // while block j is on the MFMA units, block j+1 is copied into the other
@@ -50,6 +50,8 @@
 // independent softmax chains to interleave.
 #include <math.h>
 
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -58,16 +60,19 @@ namespace {
 
 // Units per wave: enough that most units start on a block copied during
 // the previous unit, few enough that the dispatcher still balances the
-// uneven unit costs across CUs (measured best at 4 on the bge workload).
-constexpr int UNITS_PER_WAVE = 4;
+// uneven unit costs across CUs (measured best at 4 on the bge workload).  A
+// launch of fewer units than waves that fit the chip at once (8 of 20 KB LDS
+// per CU) takes one unit per wave: its time is one wave's chain, not the
+// number of waves.
+constexpr int MAX_UNITS_PER_WAVE = 4;
+constexpr int WAVES_PER_CU = 8;
 
 // DH: bytes / 2 of a unit's row slice (64: one 64-dimensional head or, with
 // PAIR, two adjacent 32-dimensional heads); n_heads counts such slices.
 template <int DH, bool PAIR>
 __global__ __launch_bounds__(64) void attention_varlen_kernel(const uint16_t* __restrict__ qkv,
                                                               uint16_t* __restrict__ out,
-                                                              const int32_t* __restrict__ cu,
-                                                              const uint32_t* __restrict__ items,
+                                                              const RowBlock* __restrict__ items,
                                                               int n_heads, float scale_log2,
                                                               int n_units) {
   constexpr int KSTEPS = DH / 16;  // MFMA steps over the row slice
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(64) void attention_varlen_kernel(const uint16_t* __
   const uint32_t lv = lds_address(sV[0]);
   constexpr uint32_t BUF = BLK * 16;
 
-  // A unit is (work item, row slice h): item = (text << 7 | 32-query block).
+  // A unit is (work item, row slice h).
   struct Unit {
     const uint16_t* base;  // Q row of the text's first token, slice h
     int q0, L, beg, h;
@@ -105,11 +110,10 @@ __global__ __launch_bounds__(64) void attention_varlen_kernel(const uint16_t* __
   auto unit_at = [&](int u) {
     Unit r;
     r.h = u % n_heads;
-    const uint32_t item = items[u / n_heads];
-    const int t = (int)(item >> 7);
-    r.q0 = (int)(item & 127u) * 32;
-    r.beg = cu[t];
-    r.L = cu[t + 1] - r.beg;
+    const RowBlock item = items[u / n_heads];
+    r.q0 = (int)(item.len_block & 127u) * 32;
+    r.beg = (int)item.beg;
+    r.L = (int)(item.len_block >> 7);
     r.base = qkv + (size_t)r.beg * ld + (size_t)r.h * DH;
     return r;
   };
@@ -330,39 +334,24 @@ __global__ __launch_bounds__(64) void attention_varlen_kernel(const uint16_t* __
 
 }  // namespace
 
-hipError_t launch_attention(const uint16_t* qkv, uint16_t* out, const int32_t* cu,
-                            const uint32_t* items, int n_items, int n_heads, int d_head,
-                            hipStream_t stream) {
+hipError_t launch_attention(const uint16_t* qkv, uint16_t* out, const RowBlock* items, int n_items,
+                            int n_heads, int d_head, int n_cus, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
   if (d_head != 64 && (d_head != 32 || n_heads % 2)) return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)d_head);
   // 32-dimensional heads go in adjacent pairs: one 64-wide row slice each.
   const int slices = d_head == 64 ? n_heads : n_heads / 2;
   const int n_units = n_items * slices;
-  const dim3 grid((unsigned)((n_units + UNITS_PER_WAVE - 1) / UNITS_PER_WAVE));
+  const int per_wave =
+      std::min(std::max(n_units / (n_cus * WAVES_PER_CU), 1), MAX_UNITS_PER_WAVE);
+  const dim3 grid((unsigned)((n_units + per_wave - 1) / per_wave));
   if (d_head == 64)
-    hipLaunchKernelGGL((attention_varlen_kernel<64, false>), grid, dim3(64), 0, stream, qkv, out, cu,
+    hipLaunchKernelGGL((attention_varlen_kernel<64, false>), grid, dim3(64), 0, stream, qkv, out,
                        items, slices, scale_log2, n_units);
   else
-    hipLaunchKernelGGL((attention_varlen_kernel<64, true>), grid, dim3(64), 0, stream, qkv, out, cu,
+    hipLaunchKernelGGL((attention_varlen_kernel<64, true>), grid, dim3(64), 0, stream, qkv, out,
                        items, slices, scale_log2, n_units);
   return hipGetLastError();
-}
-
-int row_block_items(const int64_t* cu, int64_t n_texts, uint32_t* items) {
-  // (text, 32-row block) pairs, longest text first; ties keep text order.
-  int64_t n = 0;
-  int64_t maxL = 0;
-  for (int64_t i = 0; i < n_texts; ++i) maxL = cu[i + 1] - cu[i] > maxL ? cu[i + 1] - cu[i] : maxL;
-  const int64_t max_blocks = (maxL + 31) / 32;
-  for (int64_t nb = max_blocks; nb >= 1; --nb) {
-    for (int64_t i = 0; i < n_texts; ++i) {
-      const int64_t L = cu[i + 1] - cu[i];
-      if ((L + 31) / 32 != nb) continue;
-      for (int64_t b = 0; b < nb; ++b) items[n++] = (uint32_t)((i << 7) | b);
-    }
-  }
-  return (int)n;
 }
 
 }  // namespace surge

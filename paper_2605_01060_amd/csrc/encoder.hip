@@ -7,8 +7,8 @@
 //
 // Encode one SuperBatch (Alg. 1, Flush): validate on the host, resolve every
 // text's output row pointer from the segment table, cut the SuperBatch into
-// token chunks at text boundaries, and for each chunk upload (cu_seqlens,
-// row pointers) through a pinned staging ring and launch
+// token chunks at text boundaries, and for each chunk upload (cu_seqlens, row
+// pointers, row blocks) through a pinned staging ring and launch
 //   embed+LN, then per layer: QKV, attention, O-proj+residual, LN1,
 //   FFN1+GELU, FFN2+residual, LN2, and finally pool+L2+scatter.
 // Everything is enqueued on the caller's stream; nothing blocks except the
@@ -61,9 +61,9 @@ struct surge_encoder {
   uint16_t *X = nullptr, *QKV = nullptr, *CTX = nullptr, *Y = nullptr, *H = nullptr;
   float2 *SX = nullptr, *SY = nullptr;  // row statistics partials of X and Y
   float2 *RX = nullptr, *RY = nullptr;  // their per-row LayerNorm factors
-  int32_t* d_cu = nullptr;     // [max_tokens + 1]
-  uint64_t* d_dst = nullptr;   // [max_tokens]
-  uint32_t* d_items = nullptr; // [max_tokens] attention work items
+  // Chunk metadata, packed: cu int32 [S + 1], output row pointers [S], row
+  // blocks; built in a staging slot and uploaded in one piece.
+  char* d_meta = nullptr;
   int* d_err = nullptr;
   int n_cus = 0;  // compute units of the device (GEMM grid size)
   // The workspace is shared by every call: each call's stream waits for the
@@ -72,13 +72,13 @@ struct surge_encoder {
   bool last_use_recorded = false;
   // pinned staging ring for chunk metadata
   void* staging[kStagingSlots] = {};
+  void* staging_dev[kStagingSlots] = {};  // their device mappings
   hipEvent_t staging_ev[kStagingSlots] = {};
   bool staging_used[kStagingSlots] = {};
   int staging_next = 0;
   size_t staging_bytes = 0;
   // host scratch
   std::vector<uint64_t> h_dst;
-  std::vector<int64_t> h_lcu;
   // profiling
   uint32_t prof_kinds = 0;  // bit k set: time launches of kernel class k
   std::vector<hipEvent_t> prof_events;
@@ -176,28 +176,28 @@ surge_status encode_chunks(surge_encoder* e, int64_t n_texts, const int32_t* d_t
     const int64_t S = t1 - t0;
     const int64_t T = cu[t1] - cu[t0];
 
-    // Stage (cu32 [S+1], dst [S], attention items) in a pinned slot, then
-    // copy to the device.
+    // Stage the metadata in a pinned slot and upload it with one kernel
+    // (three copies took 6 us more before the first layer could start).
     const int slot = e->staging_next;
     e->staging_next = (slot + 1) % kStagingSlots;
     if (e->staging_used[slot]) HIP_TRY(hipEventSynchronize(e->staging_ev[slot]));
+    const int n_items = (int)count_row_blocks(cu + t0, S);
+    const size_t dst_at = align_up((size_t)(S + 1) * 4, 16);
+    const size_t items_at = align_up(dst_at + (size_t)S * 8, 16);
+    const size_t meta_bytes = align_up(items_at + (size_t)n_items * sizeof(RowBlock), 16);
     char* stg = (char*)e->staging[slot];
-    const size_t cu_region = align_up((size_t)(e->max_tokens + 1) * 4, 16);
-    const size_t dst_region = (size_t)e->max_tokens * 8;
     int32_t* hcu = (int32_t*)stg;
-    uint64_t* hdst = (uint64_t*)(stg + cu_region);
-    uint32_t* hitems = (uint32_t*)(stg + cu_region + dst_region);
     for (int64_t i = 0; i <= S; ++i) hcu[i] = (int32_t)(cu[t0 + i] - cu[t0]);
-    memcpy(hdst, e->h_dst.data() + t0, (size_t)S * 8);
-    e->h_lcu.resize((size_t)S + 1);
-    for (int64_t i = 0; i <= S; ++i) e->h_lcu[(size_t)i] = cu[t0 + i] - cu[t0];
-    const int n_items = row_block_items(e->h_lcu.data(), S, hitems);
-    const size_t cu_bytes = align_up((size_t)(S + 1) * 4, 16);
-    HIP_TRY(hipMemcpyAsync(e->d_cu, hcu, cu_bytes, hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(e->d_dst, hdst, (size_t)S * 8, hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(e->d_items, hitems, (size_t)n_items * 4, hipMemcpyHostToDevice, stream));
+    memcpy(stg + dst_at, e->h_dst.data() + t0, (size_t)S * 8);
+    fill_row_blocks(cu + t0, S, (RowBlock*)(stg + items_at));
+    hipError_t ue = launch_upload(e->staging_dev[slot], e->d_meta, (int64_t)(meta_bytes / 16), stream);
+    if (ue != hipSuccess)
+      return fail(SURGE_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(ue));
     HIP_TRY(hipEventRecord(e->staging_ev[slot], stream));
     e->staging_used[slot] = true;
+    const int32_t* d_cu = (const int32_t*)e->d_meta;
+    const uint64_t* d_dst = (const uint64_t*)(e->d_meta + dst_at);
+    const RowBlock* d_items = (const RowBlock*)(e->d_meta + items_at);
 
     const int32_t* toks = d_tokens + cu[t0];
     double sumL2 = 0.0;
@@ -209,8 +209,8 @@ surge_status encode_chunks(surge_encoder* e, int64_t n_texts, const int32_t* d_t
     const int Si = (int)S;
 
     LAUNCH(SURGE_KERNEL_EMBED, 0.0, Td * (4.0 + 6.0 * d),
-           launch_embed_ln(toks, e->d_cu, e->d_items, n_items, e->word, e->pos, e->lneg,
-                           e->lneb, D.ln_eps, D.vocab_size, d, e->X, e->d_err, stream));
+           launch_embed_ln(toks, d_items, n_items, e->word, e->pos, e->lneg, e->lneb, D.ln_eps,
+                           D.vocab_size, d, e->X, e->d_err, e->n_cus, stream));
     // Post-LN with the LayerNorms folded into their neighbours: X and Y
     // hold raw (pre-LN) residual rows, SX and SY their statistics partials
     // (written by the residual GEMMs), RX and RY the per-row factors.
@@ -239,7 +239,7 @@ surge_status encode_chunks(surge_encoder* e, int64_t n_texts, const int32_t* d_t
              launch_linear(e->X, w.wqkv, w.bqkv, nullptr, e->QKV, T, 3 * d, d,
                            l == 0 ? EPI_BIAS : EPI_FOLD, xq, stream));
       LAUNCH(SURGE_KERNEL_ATTN, 4.0 * d * sumL2, 2.0 * Td * 4 * d,
-             launch_attention(e->QKV, e->CTX, e->d_cu, e->d_items, n_items, D.n_heads, dh, stream));
+             launch_attention(e->QKV, e->CTX, d_items, n_items, D.n_heads, dh, e->n_cus, stream));
       LinearExtra xo = from_x;  // O-proj + residual (LN2 of the previous layer applied to it)
       xo.stats_out = e->SY;
       xo.gamma = pw ? pw->ln2g : nullptr;
@@ -267,7 +267,7 @@ surge_status encode_chunks(surge_encoder* e, int64_t n_texts, const int32_t* d_t
     // The last layer's LN2 is applied inside the pooling.
     const LayerWeights& wl = e->layers[D.n_layers - 1];
     LAUNCH(SURGE_KERNEL_POOL, 0.0, 2.0 * Td * d + 8.0 * Td + 4.0 * S * d,
-           launch_pool_l2_scatter(e->X, e->d_cu, Si, e->d_dst, d, e->RX, wl.ln2g, wl.ln2b,
+           launch_pool_l2_scatter(e->X, d_cu, Si, d_dst, nullptr, d, e->RX, wl.ln2g, wl.ln2b,
                                   stream));
     t0 = t1;
   }
@@ -528,9 +528,9 @@ surge_status surge_encoder_create(const surge_encoder_desc* desc, const void* co
   wtake((size_t)T * d * 2);        // CTX
   wtake((size_t)T * d * 2);        // Y
   wtake((size_t)T * f * 2);        // H
-  wtake((size_t)(T + 1) * 4 + 16); // cu
-  wtake((size_t)T * 8);            // dst
-  wtake((size_t)T * 4);            // attention items
+  e->staging_bytes = align_up((size_t)(T + 1) * 4, 16) + align_up((size_t)T * 8, 16) +
+                     align_up((size_t)T * sizeof(RowBlock), 16);
+  wtake(e->staging_bytes);         // chunk metadata
   wtake(256);                      // err
   wtake((size_t)T * (d / 64) * 8); // SX: at most d/64 partials per row
   wtake((size_t)T * (d / 64) * 8); // SY
@@ -547,14 +547,12 @@ surge_status surge_encoder_create(const surge_encoder_desc* desc, const void* co
   e->CTX = (uint16_t*)(w + wo[2]);
   e->Y = (uint16_t*)(w + wo[3]);
   e->H = (uint16_t*)(w + wo[4]);
-  e->d_cu = (int32_t*)(w + wo[5]);
-  e->d_dst = (uint64_t*)(w + wo[6]);
-  e->d_items = (uint32_t*)(w + wo[7]);
-  e->d_err = (int*)(w + wo[8]);
-  e->SX = (float2*)(w + wo[9]);
-  e->SY = (float2*)(w + wo[10]);
-  e->RX = (float2*)(w + wo[11]);
-  e->RY = (float2*)(w + wo[12]);
+  e->d_meta = w + wo[5];
+  e->d_err = (int*)(w + wo[6]);
+  e->SX = (float2*)(w + wo[7]);
+  e->SY = (float2*)(w + wo[8]);
+  e->RX = (float2*)(w + wo[9]);
+  e->RY = (float2*)(w + wo[10]);
   err = hipMemset(e->d_err, 0, 256);
   if (err != hipSuccess)
     return cleanup_fail(fail(SURGE_ERR_DEVICE, "hipMemset failed: %s", hipGetErrorString(err)));
@@ -567,11 +565,15 @@ surge_status surge_encoder_create(const surge_encoder_desc* desc, const void* co
   if (err != hipSuccess)
     return cleanup_fail(fail(SURGE_ERR_DEVICE, "hipEventCreate failed: %s", hipGetErrorString(err)));
 
-  e->staging_bytes = align_up((size_t)(T + 1) * 4, 16) + (size_t)T * 8 + (size_t)T * 4;
   for (int i = 0; i < kStagingSlots; ++i) {
-    err = hipHostMalloc(&e->staging[i], e->staging_bytes, hipHostMallocDefault);
+    err = hipHostMalloc(&e->staging[i], e->staging_bytes,
+                        hipHostMallocMapped | hipHostMallocCoherent);
     if (err != hipSuccess)
       return cleanup_fail(fail(SURGE_ERR_OUT_OF_MEMORY, "hipHostMalloc failed: %s",
+                               hipGetErrorString(err)));
+    err = hipHostGetDevicePointer(&e->staging_dev[i], e->staging[i], 0);
+    if (err != hipSuccess)
+      return cleanup_fail(fail(SURGE_ERR_DEVICE, "hipHostGetDevicePointer failed: %s",
                                hipGetErrorString(err)));
     err = hipEventCreateWithFlags(&e->staging_ev[i], hipEventDisableTiming);
     if (err != hipSuccess)

@@ -33,6 +33,31 @@ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
+int64_t count_row_blocks(const int64_t* cu, int64_t n_texts) {
+  int64_t n = 0;
+  for (int64_t i = 0; i < n_texts; ++i) n += (cu[i + 1] - cu[i] + 31) / 32;
+  return n;
+}
+
+void fill_row_blocks(const int64_t* cu, int64_t n_texts, RowBlock* items) {
+  // Counting sort by the number of blocks (1 .. 128), largest first.
+  constexpr int kMax = 128;
+  int64_t first[kMax + 2] = {};  // items of texts of more than nb blocks, at [nb]
+  for (int64_t i = 0; i < n_texts; ++i) {
+    const int64_t nb = (cu[i + 1] - cu[i] + 31) / 32;
+    first[nb - 1] += nb;
+  }
+  for (int nb = kMax; nb-- > 0;) first[nb] += first[nb + 1];
+  for (int64_t i = 0; i < n_texts; ++i) {
+    const int64_t L = cu[i + 1] - cu[i];
+    const int64_t nb = (L + 31) / 32;
+    RowBlock* out = items + first[nb];
+    first[nb] += nb;
+    for (int64_t b = 0; b < nb; ++b)
+      out[b] = RowBlock{(uint32_t)(cu[i] - cu[0]), (uint32_t)(L << 7 | b)};
+  }
+}
+
 surge_status validate_desc(const surge_encoder_desc* d) {
   if (!d) return fail(SURGE_ERR_INVALID_ARGUMENT, "desc is NULL");
   if (d->n_layers < 1 || d->n_layers > 256)

@@ -6,16 +6,21 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "internal.h"
+
 namespace surge {
 
-// x_t = LN(word[id_t] + pos[t - cu_i]) for every token.  tokens [T],
-// cu int32 [n_texts+1] and the row_block_items work items (device), one
-// workgroup per item; out bf16 [T, d].  Out-of-vocabulary IDs are gathered
-// as ID 0 and set *err = 1.
-hipError_t launch_embed_ln(const int32_t* tokens, const int32_t* cu, const uint32_t* items,
-                           int n_items, const uint16_t* word, const uint16_t* pos,
-                           const float* gamma, const float* beta, float eps, int vocab, int d,
-                           uint16_t* out, int* err, hipStream_t stream);
+// Copies n16 16-byte units of pinned, device-mapped host memory to the
+// device in a kernel: one launch for a chunk's whole metadata.
+hipError_t launch_upload(const void* pinned, void* dst, int64_t n16, hipStream_t stream);
+
+// x_t = LN(word[id_t] + pos[t - cu_i]) for every token.  tokens [T], items
+// the row blocks (device); out bf16 [T, d].  Out-of-vocabulary IDs are
+// gathered as ID 0 and set *err = 1.  n_cus: compute units of the device.
+hipError_t launch_embed_ln(const int32_t* tokens, const RowBlock* items, int n_items,
+                           const uint16_t* word, const uint16_t* pos, const float* gamma,
+                           const float* beta, float eps, int vocab, int d, uint16_t* out, int* err,
+                           int n_cus, hipStream_t stream);
 
 // Y[M, N] = epi(X[M, K] W^T + b), W stored [N, K] (out, in), bf16 in/out.
 // Requires N % 128 == 0, K % 64 == 0, M >= 1.
@@ -54,7 +59,7 @@ struct LinearExtra {
   const float* col_s = nullptr;      // [N] (FOLD)
   const float* gamma = nullptr;      // [N] (LNRES)
   const float* beta = nullptr;       // [N] (LNRES)
-  int n_cus = 0;                     // compute units of the device (0: query it)
+  int n_cus = 0;                     // compute units of the device
   // Where linear_merges_stats says so, rows_in may be NULL and the factors
   // are merged from the statistics partials by the tiles that need them.
   const float2* stats_in = nullptr;
@@ -67,25 +72,20 @@ hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias
                          hipStream_t stream);
 // Whether an [M, N] linear layer can merge its input's (or residual's) row
 // statistics, `parts` partials a row, by itself (ex.stats_in), so that
-// launch_ln_rows need not run before it.  n_cus as in LinearExtra.
+// launch_ln_rows need not run before it.
 bool linear_merges_stats(int64_t M, int N, int parts, int n_cus);
+// Sets *n_cus to the current device's compute units unless it is positive.
+hipError_t resolve_cus(int* n_cus);
 // Features per statistics partial written by launch_linear for an [M, N]
 // output (the width of one wave's slice of a tile).
 int linear_stats_width(int64_t M, int N);
 
 // Packed varlen multi-head self-attention.  qkv bf16 [T, 3 H dh] (Q | K | V
 // column blocks, head h at columns h*dh of each), out bf16 [T, H dh].
-// Attention runs within each text only.  dh is 32 or 64.  items lists the
-// (text << 7 | 32-row block) work items built by row_block_items.
-hipError_t launch_attention(const uint16_t* qkv, uint16_t* out, const int32_t* cu,
-                            const uint32_t* items, int n_items, int n_heads, int d_head,
-                            hipStream_t stream);
-
-// Work items of a chunk: (text << 7 | block) for every block of 32
-// consecutive rows of a text (the attention's query blocks, the
-// embedding's row blocks); at most cu[n_texts] of them, every text length
-// in [1, 4096]; longest text first.  Returns the item count.
-int row_block_items(const int64_t* cu, int64_t n_texts, uint32_t* items);
+// Attention runs within each text only.  dh is 32 or 64.  items: the row
+// blocks (device).  n_cus: compute units of the device.
+hipError_t launch_attention(const uint16_t* qkv, uint16_t* out, const RowBlock* items, int n_items,
+                            int n_heads, int d_head, int n_cus, hipStream_t stream);
 
 // Per-row LayerNorm factors rows[m] = (rstd, -mean * rstd) from `parts`
 // equal-width statistics partials stats[p * M + m] = (mean, variance).
@@ -96,12 +96,13 @@ hipError_t launch_ln_rows(const float2* stats, int parts, int64_t M, float eps, 
 hipError_t launch_layernorm(const uint16_t* x, const float* gamma, const float* beta, float eps,
                             uint16_t* y, int64_t M, int d, hipStream_t stream);
 
-// e_i = mean of text i's rows of x; row i of the output (dst[i], a device
-// pointer to d floats) = e_i / max(||e_i||, 1e-12).  With rows != NULL the
+// e_i = mean of text i's rows of x; row i of the output (at dst[i], a device
+// pointer to d floats, or with dst == NULL at out + i d) =
+// e_i / max(||e_i||, 1e-12).  With rows != NULL the
 // rows of x are raw and LayerNorm(gamma, beta) is applied to each first,
 // from its factors rows[t] = (rstd, -mean * rstd).
 hipError_t launch_pool_l2_scatter(const uint16_t* x, const int32_t* cu, int n_texts,
-                                  const uint64_t* dst, int d, const float2* rows,
+                                  const uint64_t* dst, float* out, int d, const float2* rows,
                                   const float* gamma, const float* beta, hipStream_t stream);
 
 }  // namespace surge

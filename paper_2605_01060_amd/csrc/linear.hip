@@ -528,8 +528,7 @@ static RingTile ring_tile(int64_t M, int N, int n_cus) {
 
 int linear_stats_width(int64_t, int) { return STATS_WIDTH; }
 
-// Compute units of the current device, unless the caller knows them.
-static hipError_t resolve_cus(int* n_cus) {
+hipError_t resolve_cus(int* n_cus) {
   if (*n_cus > 0) return hipSuccess;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -538,17 +537,13 @@ static hipError_t resolve_cus(int* n_cus) {
 }
 
 bool linear_merges_stats(int64_t M, int N, int parts, int n_cus) {
-  return parts <= RING_MAX_PARTS && resolve_cus(&n_cus) == hipSuccess &&
-         ring_tile(M, N, n_cus) != RING_NONE;
+  return parts <= RING_MAX_PARTS && ring_tile(M, N, n_cus) != RING_NONE;
 }
 
 hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias, const uint16_t* R,
-                         uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& extra,
+                         uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& ex,
                          hipStream_t stream) {
   if (M <= 0) return hipSuccess;
-  LinearExtra ex = extra;
-  hipError_t e = resolve_cus(&ex.n_cus);
-  if (e != hipSuccess) return e;
   const RingTile tile = ring_tile(M, N, ex.n_cus);
   if (tile != RING_NONE)
     return launch_linear_ring(tile, X, W, bias, R, Y, M, N, K, epi, ex, stream);

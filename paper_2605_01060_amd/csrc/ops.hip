@@ -21,16 +21,27 @@ using namespace surge;
 
 namespace {
 
-// Device copy of a checked cu_seqlens (int32), freed on scope exit.
-struct DeviceCu {
-  int32_t* ptr = nullptr;
-  ~DeviceCu() {
+// Device memory freed on scope exit, with the host data copied into it on
+// `stream`.  A call waits for its stream before it returns; one that fails
+// before that (`pending`) waits here, so that neither side of the copy is
+// freed under it.
+struct DeviceBuf {
+  std::vector<uint32_t> host;
+  void* ptr = nullptr;
+  hipStream_t stream = nullptr;
+  bool pending = false;
+  ~DeviceBuf() {
+    if (pending) (void)hipStreamSynchronize(stream);
     if (ptr) hipFree(ptr);
+  }
+  hipError_t wait() {
+    const hipError_t e = hipStreamSynchronize(stream);
+    pending = false;
+    return e;
   }
 };
 
-surge_status upload_cu(int64_t n_texts, const int64_t* cu, int64_t max_len, DeviceCu* out,
-                       int64_t* n_tokens) {
+surge_status check_cu(int64_t n_texts, const int64_t* cu, int64_t max_len) {
   if (n_texts < 1) return fail(SURGE_ERR_INVALID_ARGUMENT, "n_texts=%lld < 1", (long long)n_texts);
   if (!cu) return fail(SURGE_ERR_INVALID_ARGUMENT, "cu_seqlens is NULL");
   if (cu[0] != 0) return fail(SURGE_ERR_INVALID_ARGUMENT, "cu_seqlens[0] != 0");
@@ -41,12 +52,26 @@ surge_status upload_cu(int64_t n_texts, const int64_t* cu, int64_t max_len, Devi
                   (long long)i, (long long)L, (long long)max_len);
   }
   if (cu[n_texts] > (int64_t)INT32_MAX) return fail(SURGE_ERR_INVALID_ARGUMENT, "too many tokens");
-  std::vector<int32_t> h((size_t)n_texts + 1);
-  for (int64_t i = 0; i <= n_texts; ++i) h[(size_t)i] = (int32_t)cu[i];
-  HIP_TRY(hipMalloc(&out->ptr, h.size() * 4));
-  HIP_TRY(hipMemcpy(out->ptr, h.data(), h.size() * 4, hipMemcpyHostToDevice));
-  *n_tokens = cu[n_texts];
   return SURGE_OK;
+}
+
+// One device block of the buffer's host words and one copy on the stream.
+surge_status upload(DeviceBuf* buf, hipStream_t s) {
+  HIP_TRY(hipMalloc(&buf->ptr, buf->host.size() * 4));
+  buf->stream = s;
+  buf->pending = true;
+  HIP_TRY(hipMemcpyAsync(buf->ptr, buf->host.data(), buf->host.size() * 4, hipMemcpyHostToDevice, s));
+  return SURGE_OK;
+}
+
+// The row blocks of a checked cu_seqlens, after `head` words of zeros.
+surge_status upload_items(int64_t n_texts, const int64_t* cu, int head, DeviceBuf* buf, int* n_items,
+                          hipStream_t s) {
+  const int64_t n = count_row_blocks(cu, n_texts);
+  *n_items = (int)n;
+  buf->host.resize((size_t)(head + 2 * n));
+  fill_row_blocks(cu, n_texts, (RowBlock*)(buf->host.data() + head));
+  return upload(buf, s);
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -97,26 +122,19 @@ surge_status surge_op_embed_ln(int64_t n_texts, const int64_t* cu, const int32_t
   if (!aligned16(d_word) || !aligned16(d_pos) || !aligned16(d_gamma) || !aligned16(d_beta) ||
       !aligned16(d_out))
     return fail(SURGE_ERR_INVALID_ARGUMENT, "device buffers must be 16-byte aligned");
-  DeviceCu dcu;
-  int64_t T = 0;
-  surge_status st = upload_cu(n_texts, cu, std::min(max_pos, 4096), &dcu, &T);
+  surge_status st = check_cu(n_texts, cu, std::min(max_pos, 4096));
   if (st != SURGE_OK) return st;
-  std::vector<uint32_t> items((size_t)T);
-  const int n_items = row_block_items(cu, n_texts, items.data());
-  DeviceCu ditems;
-  HIP_TRY(hipMalloc(&ditems.ptr, (size_t)n_items * 4));
-  HIP_TRY(hipMemcpy(ditems.ptr, items.data(), (size_t)n_items * 4, hipMemcpyHostToDevice));
-  int* derr = nullptr;
-  HIP_TRY(hipMalloc(&derr, sizeof(int)));
-  DeviceCu guard;  // frees derr through the same path
-  guard.ptr = (int32_t*)derr;
-  HIP_TRY(hipMemset(derr, 0, sizeof(int)));
   hipStream_t s = (hipStream_t)hip_stream;
-  HIP_TRY(launch_embed_ln(d_tokens, dcu.ptr, (const uint32_t*)ditems.ptr, n_items, d_word, d_pos,
-                          d_gamma, d_beta, eps, vocab, d, d_out, derr, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  int n_cus = 0, n_items = 0;
+  HIP_TRY(resolve_cus(&n_cus));
+  DeviceBuf meta;  // the error flag (and a word of padding), then the row blocks
+  st = upload_items(n_texts, cu, 2, &meta, &n_items, s);
+  if (st != SURGE_OK) return st;
+  HIP_TRY(launch_embed_ln(d_tokens, (const RowBlock*)((int32_t*)meta.ptr + 2), n_items, d_word, d_pos,
+                          d_gamma, d_beta, eps, vocab, d, d_out, (int*)meta.ptr, n_cus, s));
   int flag = 0;
-  HIP_TRY(hipMemcpy(&flag, derr, sizeof(int), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpyAsync(&flag, meta.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIP_TRY(meta.wait());
   if (flag) return fail(SURGE_ERR_INVALID_ARGUMENT, "a token ID outside [0, vocab) was read as 0");
   return SURGE_OK;
 }
@@ -135,7 +153,9 @@ surge_status surge_op_linear(int64_t M, int32_t N, int32_t K, const uint16_t* d_
       (d_res && !aligned16(d_res)))
     return fail(SURGE_ERR_INVALID_ARGUMENT, "device buffers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)hip_stream;
-  HIP_TRY(launch_linear(d_x, d_w, d_bias, d_res, d_y, M, N, K, epilogue, LinearExtra(), s));
+  LinearExtra ex;
+  HIP_TRY(resolve_cus(&ex.n_cus));
+  HIP_TRY(launch_linear(d_x, d_w, d_bias, d_res, d_y, M, N, K, epilogue, ex, s));
   HIP_TRY(hipStreamSynchronize(s));
   return SURGE_OK;
 }
@@ -184,8 +204,9 @@ surge_status enqueue_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* 
                                int32_t epilogue, const float* d_stats_in, int32_t parts_in,
                                const float* d_col_s, const float* d_gamma, const float* d_beta,
                                float eps, float* d_stats_out, uint16_t* d_y, float2* rows,
-                               hipStream_t s) {
+                               int n_cus, hipStream_t s) {
   LinearExtra ex;
+  ex.n_cus = n_cus;
   ex.stats_out = (float2*)d_stats_out;
   ex.col_s = d_col_s;
   ex.gamma = d_gamma;
@@ -217,10 +238,12 @@ surge_status surge_op_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t*
                                     &factors);
   if (st != SURGE_OK) return st;
   hipStream_t s = (hipStream_t)hip_stream;
-  DeviceCu rows;  // per-row LayerNorm factors, freed on return
-  if (factors && !linear_merges_stats(M, N, parts_in, 0)) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
+  int n_cus = 0;
+  HIP_TRY(resolve_cus(&n_cus));
+  DeviceBuf rows;  // per-row LayerNorm factors, freed on return
+  if (factors && !linear_merges_stats(M, N, parts_in, n_cus)) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
   st = enqueue_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in, parts_in, d_col_s,
-                         d_gamma, d_beta, eps, d_stats_out, d_y, (float2*)rows.ptr, s);
+                         d_gamma, d_beta, eps, d_stats_out, d_y, (float2*)rows.ptr, n_cus, s);
   if (st != SURGE_OK) return st;
   HIP_TRY(hipStreamSynchronize(s));
   return SURGE_OK;
@@ -243,12 +266,14 @@ surge_status surge_op_linear_ln_noalloc(int64_t M, int32_t N, int32_t K, const u
   if (factors && M > kScratchRows)
     return fail(SURGE_ERR_CAPACITY, "M=%lld rows exceed the %lld rows of the static scratch",
                 (long long)M, (long long)kScratchRows);
-  if (factors && !linear_merges_stats(M, N, parts_in, 0)) {
+  int n_cus = 0;
+  HIP_TRY(resolve_cus(&n_cus));
+  if (factors && !linear_merges_stats(M, N, parts_in, n_cus)) {
     st = scratch_address(&rows);
     if (st != SURGE_OK) return st;
   }
   return enqueue_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in, parts_in,
-                           d_col_s, d_gamma, d_beta, eps, d_stats_out, d_y, rows,
+                           d_col_s, d_gamma, d_beta, eps, d_stats_out, d_y, rows, n_cus,
                            (hipStream_t)hip_stream);
 }
 
@@ -263,19 +288,17 @@ surge_status surge_op_attention(int64_t n_texts, const int64_t* cu, int32_t n_he
   if (!d_qkv || !d_out) return fail(SURGE_ERR_INVALID_ARGUMENT, "NULL device pointer");
   if (!aligned16(d_qkv) || !aligned16(d_out))
     return fail(SURGE_ERR_INVALID_ARGUMENT, "device buffers must be 16-byte aligned");
-  DeviceCu dcu;
-  int64_t T = 0;
-  surge_status st = upload_cu(n_texts, cu, 4096, &dcu, &T);
+  surge_status st = check_cu(n_texts, cu, 4096);
   if (st != SURGE_OK) return st;
-  std::vector<uint32_t> items((size_t)T);
-  const int n_items = row_block_items(cu, n_texts, items.data());
-  DeviceCu ditems;
-  HIP_TRY(hipMalloc(&ditems.ptr, (size_t)n_items * 4));
-  HIP_TRY(hipMemcpy(ditems.ptr, items.data(), (size_t)n_items * 4, hipMemcpyHostToDevice));
   hipStream_t s = (hipStream_t)hip_stream;
-  HIP_TRY(launch_attention(d_qkv, d_out, dcu.ptr, (const uint32_t*)ditems.ptr, n_items, n_heads,
-                           d_head, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  int n_cus = 0, n_items = 0;
+  HIP_TRY(resolve_cus(&n_cus));
+  DeviceBuf items;
+  st = upload_items(n_texts, cu, 0, &items, &n_items, s);
+  if (st != SURGE_OK) return st;
+  HIP_TRY(launch_attention(d_qkv, d_out, (const RowBlock*)items.ptr, n_items, n_heads, d_head, n_cus,
+                           s));
+  HIP_TRY(items.wait());
   return SURGE_OK;
 }
 
@@ -300,19 +323,17 @@ surge_status surge_op_pool_l2(int64_t n_texts, const int64_t* cu, int32_t d, con
   if (!d_x || !d_out) return fail(SURGE_ERR_INVALID_ARGUMENT, "NULL device pointer");
   if (!aligned16(d_x) || !aligned16(d_out))
     return fail(SURGE_ERR_INVALID_ARGUMENT, "device buffers must be 16-byte aligned");
-  DeviceCu dcu;
-  int64_t T = 0;
-  surge_status st = upload_cu(n_texts, cu, 1 << 16, &dcu, &T);
+  surge_status st = check_cu(n_texts, cu, 1 << 16);
   if (st != SURGE_OK) return st;
-  std::vector<uint64_t> rows((size_t)n_texts);
-  for (int64_t i = 0; i < n_texts; ++i) rows[(size_t)i] = (uint64_t)(uintptr_t)(d_out + i * d);
-  DeviceCu drows;
-  HIP_TRY(hipMalloc(&drows.ptr, rows.size() * 8));
-  HIP_TRY(hipMemcpy(drows.ptr, rows.data(), rows.size() * 8, hipMemcpyHostToDevice));
   hipStream_t s = (hipStream_t)hip_stream;
-  HIP_TRY(launch_pool_l2_scatter(d_x, dcu.ptr, (int)n_texts, (const uint64_t*)drows.ptr, d,
+  DeviceBuf dcu;
+  dcu.host.resize((size_t)n_texts + 1);
+  for (int64_t i = 0; i <= n_texts; ++i) dcu.host[(size_t)i] = (uint32_t)cu[i];
+  st = upload(&dcu, s);
+  if (st != SURGE_OK) return st;
+  HIP_TRY(launch_pool_l2_scatter(d_x, (const int32_t*)dcu.ptr, (int)n_texts, nullptr, d_out, d,
                                  nullptr, nullptr, nullptr, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(dcu.wait());
   return SURGE_OK;
 }
 

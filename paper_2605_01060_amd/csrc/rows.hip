@@ -59,61 +59,80 @@ __device__ __forceinline__ void ln_row(float (&v)[MAXC][8], int nch, int lane, i
   }
 }
 
-// One block per work item (text t, rows 32b .. 32b+31 of it), so a long
-// text is spread over several blocks instead of keeping one block busy to
-// the end of the launch; the block's four waves take the item's rows in
-// turn.  A wave fetches its next row's token ID and table chunks before it
-// normalises the current row, so one row's gather latency hides behind the
-// previous row's work.
+// One workgroup per `rows` rows of a work item (a 32-row block of a text),
+// so a long text is spread over several workgroups; the four waves take its
+// rows in turn.  A wave loads all its token IDs at once (one per lane) and
+// fetches a row's table chunks two rows ahead of the LayerNorm, so the
+// gathers of three rows are in flight.
 __global__ __launch_bounds__(256) void embed_ln_kernel(
-    const int32_t* __restrict__ tokens, const int32_t* __restrict__ cu,
-    const uint32_t* __restrict__ items, const uint16_t* __restrict__ word,
-    const uint16_t* __restrict__ pos, const float* __restrict__ gamma,
-    const float* __restrict__ beta, float eps, int vocab, int d, uint16_t* __restrict__ out,
-    int* __restrict__ err) {
-  const uint32_t item = items[blockIdx.x];
-  const int t = (int)(item >> 7);
+    const int32_t* __restrict__ tokens, const RowBlock* __restrict__ items, int rows,
+    const uint16_t* __restrict__ word, const uint16_t* __restrict__ pos,
+    const float* __restrict__ gamma, const float* __restrict__ beta, float eps, int vocab, int d,
+    uint16_t* __restrict__ out, int* __restrict__ err) {
+  const RowBlock item = items[blockIdx.x];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int beg = cu[t];
-  const int r0 = (int)(item & 127u) * 32;           // first row of the item
-  const int r1 = min(r0 + 32, cu[t + 1] - beg);     // one past its last
+  const int beg = (int)item.beg;
+  const int r0 = (int)(item.len_block & 127u) * 32 + (int)blockIdx.y * rows + wave;
+  const int r1 = min((int)(item.len_block & 127u) * 32 + ((int)blockIdx.y + 1) * rows,
+                     (int)(item.len_block >> 7));
+  if (r0 >= r1) return;
+  const int n = (r1 - r0 + 3) >> 2;  // this wave's rows: r0, r0 + 4, ...
   const int nch = d >> 3;
-  // Table chunks of row p (word row of its checked ID, position row p).
-  auto fetch = [&](int p, uint4 (&w)[MAXC], uint4 (&q)[MAXC]) {
-    int id = tokens[beg + p];
-    if (id < 0 || id >= vocab) {
-      if (lane == 0) atomicOr(err, 1);
-      id = 0;
+  int ids = 0;
+  if (lane < n) {
+    ids = tokens[beg + r0 + 4 * lane];
+    if (ids < 0 || ids >= vocab) {
+      atomicOr(err, 1);
+      ids = 0;
     }
+  }
+  uint4 w[3][MAXC], q[3][MAXC];
+  // Table chunks of the wave's i-th row (word row of its checked ID,
+  // position row).
+  auto fetch = [&](int i, int slot) {
+    const int id = __builtin_amdgcn_readlane(ids, i);
     const uint4* wr = reinterpret_cast<const uint4*>(word + (size_t)id * d);
-    const uint4* pr = reinterpret_cast<const uint4*>(pos + (size_t)p * d);
+    const uint4* pr = reinterpret_cast<const uint4*>(pos + (size_t)(r0 + 4 * i) * d);
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
       const int ch = lane + 64 * c;
       if (ch < nch) {
-        w[c] = wr[ch];
-        q[c] = pr[ch];
+        w[slot][c] = wr[ch];
+        q[slot][c] = pr[ch];
       }
     }
   };
-  uint4 wn[MAXC], qn[MAXC];
-  if (r0 + wave < r1) fetch(r0 + wave, wn, qn);
-  for (int p = r0 + wave; p < r1; p += 4) {
+  auto row = [&](int i, int slot) {
     float v[MAXC][8];
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
       if (lane + 64 * c < nch) {
         float a[8], b[8];
-        unpack8(wn[c], a);
-        unpack8(qn[c], b);
+        unpack8(w[slot][c], a);
+        unpack8(q[slot][c], b);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[c][e] = a[e] + b[e];
       }
     }
-    if (p + 4 < r1) fetch(p + 4, wn, qn);
-    ln_row(v, nch, lane, d, gamma, beta, eps, out + (size_t)(beg + p) * d);
+    if (i + 3 < n) fetch(i + 3, slot);
+    ln_row(v, nch, lane, d, gamma, beta, eps, out + (size_t)(beg + r0 + 4 * i) * d);
+  };
+  fetch(0, 0);
+  if (n > 1) fetch(1, 1);
+  if (n > 2) fetch(2, 2);
+  for (int i = 0; i < n; i += 3) {
+    row(i, 0);
+    if (i + 1 < n) row(i + 1, 1);
+    if (i + 2 < n) row(i + 2, 2);
   }
+}
+
+// 16 bytes per thread from mapped host memory.
+__global__ __launch_bounds__(256) void upload_kernel(const uint4* __restrict__ src,
+                                                     uint4* __restrict__ dst, int64_t n16) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) dst[i] = src[i];
 }
 
 // One wave per row, four rows per block.
@@ -145,7 +164,8 @@ template <bool LN>
 __global__ __launch_bounds__(256) void pool_l2_scatter_kernel(const uint16_t* __restrict__ x,
                                                               const int32_t* __restrict__ cu,
                                                               const uint64_t* __restrict__ dst,
-                                                              int d, const float2* __restrict__ rows,
+                                                              float* __restrict__ out, int d,
+                                                              const float2* __restrict__ rows,
                                                               const float* __restrict__ gamma,
                                                               const float* __restrict__ beta) {
   __shared__ float part[128 * 8];
@@ -195,7 +215,7 @@ __global__ __launch_bounds__(256) void pool_l2_scatter_kernel(const uint16_t* __
   const float norm = sqrtf(red[0] + red[1]);
   const float inv = 1.0f / fmaxf(norm, 1e-12f);
   if (grp == 0 && c < nch) {
-    float* row = reinterpret_cast<float*>(dst[t]);
+    float* row = dst ? reinterpret_cast<float*>(dst[t]) : out + (size_t)t * d;
     float4 a = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
     float4 b = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
     reinterpret_cast<float4*>(row)[2 * c] = a;
@@ -218,13 +238,24 @@ __global__ __launch_bounds__(256) void ln_rows_kernel(const float2* __restrict__
 
 }  // namespace
 
-hipError_t launch_embed_ln(const int32_t* tokens, const int32_t* cu, const uint32_t* items,
-                           int n_items, const uint16_t* word, const uint16_t* pos,
-                           const float* gamma, const float* beta, float eps, int vocab, int d,
-                           uint16_t* out, int* err, hipStream_t stream) {
+hipError_t launch_embed_ln(const int32_t* tokens, const RowBlock* items, int n_items,
+                           const uint16_t* word, const uint16_t* pos, const float* gamma,
+                           const float* beta, float eps, int vocab, int d, uint16_t* out, int* err,
+                           int n_cus, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(embed_ln_kernel, dim3(n_items), dim3(256), 0, stream, tokens, cu, items, word,
-                     pos, gamma, beta, eps, vocab, d, out, err);
+  // Whole 32-row items once they fill the chip (8 workgroups per CU);
+  // fewer rows per workgroup, down to one per wave, while they do not.
+  int split = 1;
+  while (split < 8 && (int64_t)n_items * split * 2 <= (int64_t)n_cus * 8) split *= 2;
+  hipLaunchKernelGGL(embed_ln_kernel, dim3(n_items, split), dim3(256), 0, stream, tokens, items,
+                     32 / split, word, pos, gamma, beta, eps, vocab, d, out, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const void* pinned, void* dst, int64_t n16, hipStream_t stream) {
+  if (n16 <= 0) return hipSuccess;
+  hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, stream,
+                     (const uint4*)pinned, (uint4*)dst, n16);
   return hipGetLastError();
 }
 
@@ -250,15 +281,15 @@ hipError_t launch_layernorm(const uint16_t* x, const float* gamma, const float* 
 }
 
 hipError_t launch_pool_l2_scatter(const uint16_t* x, const int32_t* cu, int n_texts,
-                                  const uint64_t* dst, int d, const float2* rows,
+                                  const uint64_t* dst, float* out, int d, const float2* rows,
                                   const float* gamma, const float* beta, hipStream_t stream) {
   if (n_texts <= 0) return hipSuccess;
   if (rows)
     hipLaunchKernelGGL(pool_l2_scatter_kernel<true>, dim3(n_texts), dim3(256), 0, stream, x, cu,
-                       dst, d, rows, gamma, beta);
+                       dst, out, d, rows, gamma, beta);
   else
     hipLaunchKernelGGL(pool_l2_scatter_kernel<false>, dim3(n_texts), dim3(256), 0, stream, x, cu,
-                       dst, d, rows, gamma, beta);
+                       dst, out, d, rows, gamma, beta);
   return hipGetLastError();
 }
 
