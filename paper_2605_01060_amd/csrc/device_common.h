@@ -108,6 +108,16 @@ __device__ __forceinline__ void copy_to_lds4(const void* g, uint32_t lds) {
       : "memory", "m0");
 }
 
+__device__ __forceinline__ void copy_to_lds4_at(const void* sbase, uint32_t voff, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %0, %1"
+      :
+      : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds))
+      : "memory", "m0");
+}
+
 // The same copy from sbase + voff: sbase wave-uniform (scalar registers),
 // voff a 32-bit byte offset per lane.
 __device__ __forceinline__ void copy_to_lds16_at(const void* sbase, uint32_t voff, uint32_t lds) {
@@ -117,6 +127,29 @@ __device__ __forceinline__ void copy_to_lds16_at(const void* sbase, uint32_t vof
       "global_load_lds_dwordx4 %0, %1"
       :
       : "v"(voff), "s"(sbase), "s"(lds)
+      : "memory", "m0");
+}
+
+// The same with every lane on or off by `mask` (wave-uniform, ~0 or 0), for
+// copies that may have to be skipped without a branch between the MFMAs
+// around them.  Needs all 64 lanes active.  lane_mask makes such a mask and
+// keeps it in a scalar register (the compiler folds a plain readfirstlane of
+// a select away and may leave the select in a vector register).
+__device__ __forceinline__ uint32_t lane_mask(bool on) {
+  uint32_t v = on ? ~0u : 0u;
+  asm volatile("" : "+v"(v));
+  return __builtin_amdgcn_readfirstlane(v);
+}
+__device__ __forceinline__ void copy_to_lds16_if(const void* sbase, uint32_t voff, uint32_t lds,
+                                                 uint32_t mask) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_mov_b32 exec_lo, %3\n\t"
+      "s_mov_b32 exec_hi, %3\n\t"
+      "global_load_lds_dwordx4 %0, %1\n\t"
+      "s_mov_b64 exec, -1"
+      :
+      : "v"(voff), "s"(sbase), "s"(lds), "s"(mask)
       : "memory", "m0");
 }
 

@@ -10,9 +10,11 @@
 // units; one barrier per stage publishes the next buffer and frees the
 // current one.
 //
-// The same 32x32x16 MFMAs in the same K order, the same 64-feature
-// statistics partials and the same finish as the large tiles: a row's
-// result does not depend on which kernel computed it.
+// 32x32x16 MFMAs: half as many instructions on the tile's chain as the large
+// tiles' 16x16x32 (one bge query 364 against 405 us), the same bits, and
+// power does not count here.  The same K order, 64-feature statistics
+// partials (summed in the same order) and finish too: a row's result does
+// not depend on which kernel computed it.
 //
 // LayerNorm factors can come straight from the statistics partials of the
 // producing layer (ex.stats_in): each tile merges its own rows' partials, so
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void linear_ring_kernel(
   __shared__ u32x4 sT[BN * BM / 8];
   __shared__ float4 svec[NV][BN / 4];
   __shared__ float2 spart[FACTORS ? RING_MAX_PARTS * BM : 1];
-  __shared__ float2 sxch[STATS && TN == 1 ? (WAVES_N / 2) * BM * 2 : 1];
+  __shared__ float4 sxch[STATS && TN == 1 ? (WAVES_N / 2) * BM * 2 : 1];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -293,23 +295,30 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void linear_ring_kernel(
       }
 
   // Row statistics over 64 features: one wave's two accumulator tiles, or
-  // (TN = 1) a pair of waves, the second continuing the first's sums in the
-  // one-wave order.
+  // (TN = 1) a pair of waves, the second continuing the first's sums.  In
+  // the 16x16x32 layout of the large tiles the four lanes of a token hold
+  // features 4q .. 4q+3 of every 16; this lane holds those of q = lhi (even
+  // g) and of q = 2 + lhi (odd g), summed apart to add up in the same order.
   if constexpr (STATS) {
-    float ss[TM], sq[TM];
+    float ss[TM][2], sq[TM][2];
     auto add = [&](int i, int j) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) row_stats_add(out[i][j][g], ss[j], sq[j]);
+      for (int g = 0; g < 4; ++g) row_stats_add(out[i][j][g], ss[j][g & 1], sq[j][g & 1]);
     };
     auto finish = [&](int j) {
-      const float s1 = ss[j] + __shfl_xor(ss[j], 32, 64);
-      const float q1 = sq[j] + __shfl_xor(sq[j], 32, 64);
+      float s2[2], q2[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        s2[h] = ss[j][h] + __shfl_xor(ss[j][h], 32, 64);
+        q2[h] = sq[j][h] + __shfl_xor(sq[j][h], 32, 64);
+      }
       const int m = m0 + wm0 + j * 32 + l32;
       if (lhi == 0 && m < M)
-        ex.stats_out[(size_t)((n0 + wn0) / STATS_WIDTH) * M + m] = row_stats_finish(s1, q1);
+        ex.stats_out[(size_t)((n0 + wn0) / STATS_WIDTH) * M + m] =
+            row_stats_finish(s2[0] + s2[1], q2[0] + q2[1]);
     };
 #pragma unroll
-    for (int j = 0; j < TM; ++j) ss[j] = sq[j] = 0.0f;
+    for (int j = 0; j < TM; ++j) ss[j][0] = ss[j][1] = sq[j][0] = sq[j][1] = 0.0f;
     if constexpr (TN == 2) {
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
@@ -318,21 +327,23 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void linear_ring_kernel(
         finish(j);
       }
     } else {
-      float2* x = sxch + (wave_n / 2) * BM * 2;
+      float4* x = sxch + (wave_n / 2) * BM * 2;
       if (wave_n % 2 == 0) {
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
           add(0, j);
-          x[(wm0 + j * 32 + l32) * 2 + lhi] = make_float2(ss[j], sq[j]);
+          x[(wm0 + j * 32 + l32) * 2 + lhi] = make_float4(ss[j][0], ss[j][1], sq[j][0], sq[j][1]);
         }
       }
       __syncthreads();
       if (wave_n % 2 == 1) {
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
-          const float2 v = x[(wm0 + j * 32 + l32) * 2 + lhi];
-          ss[j] = v.x;
-          sq[j] = v.y;
+          const float4 v = x[(wm0 + j * 32 + l32) * 2 + lhi];
+          ss[j][0] = v.x;
+          ss[j][1] = v.y;
+          sq[j][0] = v.z;
+          sq[j][1] = v.w;
           add(0, j);
           finish(j);
         }

@@ -1,0 +1,305 @@
+// Token-major linear layers of large chunks (gfx950): Y = epi(X W^T + b) in
+// 256 x 256 tiles, one persistent 8-wave workgroup per CU, each wave a 64
+// token x 128 feature sub-tile of 16x16x32 bf16 MFMAs.
+//
+// What bounds it: the power limit and late operand copies.  On normal data
+// (K = 3072, TFLOP/s) a loop that gave each copy one K stage to arrive ran at
+// 1,160, with copies that all hit the L2 at 1,335 and without copies at
+// 1,600; on zeros, where power does not count, 1,390, 1,918 and 1,966.  Hence
+// the MFMA that needs less power (linear_common.h) and a schedule that gives
+// copies more time.  128 KB of LDS hold two 64-wide stages of a tile whatever
+// the schedule, so this one frees LDS earlier: a wave keeps a whole stage's W
+// fragments in registers;
+// a stage runs as two phases, token half j = 0 then j = 1 of the wave's rows
+// against the same 16 W fragments, and each W fragment is replaced by the
+// next stage's right after its last MFMA.  So
+//   - W and the j = 0 rows of stage s are read out by the end of stage s-1,
+//     and their LDS takes stage s+2 from there on (barrier B, placed after
+//     the first four MFMAs of stage s so that no wave waits for its reads);
+//   - the j = 1 rows of stage s are read out by the middle of stage s
+//     (barrier A, between the phases), and theirs takes stage s+2.
+// Every copy has one and a half stages to arrive, and the MFMAs after either
+// barrier find their operands in registers.  The copies are spread over the
+// MFMAs, since a burst of them blocks the issue of everything behind it.
+//
+// The copy stream runs on across tile boundaries.  Only the j = 1 rows of
+// the next tile's second stage are held back: their LDS (8 of the 16 KB of a
+// wave's copy slots) and 16 KB beside the stages are the waves' epilogue
+// regions.  The accumulators see the same K order as every other tile shape.
+//
+// Measured against the loop of one-stage tolerance on 32x32x16 MFMAs that it
+// replaces (M = 262,144, us): QKV 898 -> 828, FFN2 1,132 -> 1,061, FFN1
+// 1,390 -> 1,309, O-projection 375 -> 364.
+#include <algorithm>
+
+#include "linear_common.h"
+
+namespace surge {
+namespace {
+
+__device__ __forceinline__ bf16x8 lds_fragment(uint32_t addr) {
+  return __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4*)addr);
+}
+
+template <int EPI, int ORDER>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void linear_wide_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, const float* __restrict__ bias,
+    const uint16_t* __restrict__ R, uint16_t* __restrict__ Y, int M, int N, int K, int tiles_n,
+    int n_tiles, LinearExtra ex) {
+  constexpr int BM = 256, BN = 256, TI = 8, TJ = 4;
+  // LDS, in bytes from smem: W of stage parity p at p * BUF; the j rows of X
+  // at X0 + p * BUF + j * HALF; the spare halves of the epilogue regions.
+  constexpr uint32_t BUF = 32768, HALF = 16384, X0 = 65536, SPARE = 131072;
+  constexpr bool FOLD = EPI == EPI_FOLD || EPI == EPI_FOLD_GELU;
+  constexpr bool LNRES = EPI == EPI_LNRES_STATS;
+  constexpr int NV = 1 + (FOLD ? 1 : 0) + (LNRES ? 2 : 0);
+  __shared__ u32x4 smem[(SPARE + HALF) / 16];
+  // Per-feature vectors (bias, then col_s or gamma and beta) by tile parity.
+  __shared__ float4 svec[2][NV][BN / 4];
+  __shared__ float2 srow[2][FOLD || LNRES ? BM : 1];  // LayerNorm factors of the tile's rows
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_m = wave >> 1;
+  const int wn0 = (wave & 1) * 128;
+  const int wm0 = wave_m * 64;
+  const int nkt = K / 64;
+  const int G = gridDim.x;
+
+  // Fragment addresses of stage parity 0: row lane % 16, then the swizzled
+  // 16-byte chunk of the 32-wide K step ks; fragments are 16 rows apart.
+  const uint32_t lds = lds_address(smem);
+  uint32_t aw[2], ax[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const uint32_t ch = (uint32_t)swz<8>(lane & 15, ks * 4 + (lane >> 4)) * 16u;
+    aw[ks] = lds + (uint32_t)wn0 * 128u + ch;
+    ax[ks] = lds + X0 + (uint32_t)wave_m * 4096u + ch;
+  }
+  bf16x8 fw[TI][2], f0[2][2], f1[2][2];  // W; the j = 0 and j = 1 rows
+  auto read_w = [&](int i, int ks) { fw[i][ks] = lds_fragment(aw[ks] + i * 2048); };
+  auto read_x0 = [&](int jj, int ks) { f0[jj][ks] = lds_fragment(ax[ks] + jj * 2048); };
+  auto read_x1 = [&](int jj, int ks) { f1[jj][ks] = lds_fragment(ax[ks] + HALF + jj * 2048); };
+
+  // Copies.  A wave instruction fills 8 rows of 128 bytes; the 32 rows of
+  // wave_m in half j of X are tile rows wave_m * 64 + j * 32 + 0 .. 31.
+  const uint32_t ldsw = __builtin_amdgcn_readfirstlane(lds + wave * 1024);
+  int it_tile = blockIdx.x;  // the copy stream's tile and stage
+  int it_kt = 0;
+  const uint16_t* xs;
+  const uint16_t* ws;
+  uint32_t xo[4];
+  const uint32_t wo = __umul24((uint32_t)(wave * 8 + (lane >> 3)), (uint32_t)K * 2u) +
+                      (uint32_t)copy_chunk<8>(lane, wave) * 16u;
+  // A copy of the lane index that the compiler cannot see through: what is
+  // derived from it is computed where it is used and not kept in registers
+  // over the main loop, which has none to spare.
+  auto opaque_lane = [&]() {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  auto point = [&]() {
+    int tm_, tn_;
+    tile_coords<ORDER>(it_tile, n_tiles, tiles_n, &tm_, &tn_);
+    xs = X + (size_t)(tm_ * BM) * K;
+    ws = W + (size_t)(tn_ * BN) * K;
+    const int l = opaque_lane();
+    const int lr = wave * 8 + (l >> 3);
+    const int row0 = (lr >> 5) * 64 + (lr & 31);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {  // half q / 2, copy q % 2; rows past M: clamped
+      const int row = min(row0 + (q >> 1) * 32 + (q & 1) * 128, M - 1 - tm_ * BM);
+      xo[q] = __umul24((uint32_t)row, (uint32_t)K * 2u) + (uint32_t)copy_chunk<8>(l, wave) * 16u;
+    }
+  };
+  // Copy c of the cursor's stage into parity p, skipped where `go` is 0:
+  // 0 .. 3 W, 4 .. 5 the j = 0 rows, 6 .. 7 the j = 1 rows.
+  auto copy = [&](int c, uint32_t p, uint32_t go) {
+    const uint32_t base = ldsw + p * BUF;
+    if (c < 4)
+      copy_to_lds16_if(ws + (size_t)(c * 64) * K + it_kt * 64, wo, base + c * 8192, go);
+    else
+      copy_to_lds16_if(xs + it_kt * 64, xo[c - 4],
+                       base + X0 + ((c - 4) >> 1) * HALF + ((c - 4) & 1) * 8192, go);
+  };
+  auto advance = [&]() {
+    if (++it_kt == nkt) {
+      it_kt = 0;
+      it_tile += G;
+      if (it_tile < n_tiles) point();
+    }
+  };
+  auto more = [&]() { return lane_mask(it_tile < n_tiles); };
+
+  int t = blockIdx.x;  // < n_tiles: the grid is never larger than the tile count
+  point();
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const uint32_t go = more();
+#pragma unroll
+    for (int c = 0; c < 8; ++c) copy(c, s, go);
+    if (s == 0 || go) advance();
+  }
+  if (more())
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  uint32_t p = 0;  // parity of the stage being computed
+  int tpar = 0;
+  bool first = true;
+
+  for (;;) {
+    int tm, tn;
+    tile_coords<ORDER>(t, n_tiles, tiles_n, &tm, &tn);
+    const int m0 = tm * BM;
+    const int n0 = tn * BN;
+
+    // Per-feature vectors, wave w copying vector w, and the row factors;
+    // published by the barriers of the tile's first stages, last read two
+    // tiles ago.
+    if (wave < NV) {
+      const float* src = bias;
+      if constexpr (FOLD) { if (wave == 1) src = ex.col_s; }
+      if constexpr (LNRES) { if (wave == 1) src = ex.gamma; if (wave == 2) src = ex.beta; }
+      copy_lanes_to_lds16(src + n0, lds_address(&svec[tpar][wave][0]));
+    }
+    if constexpr (FOLD || LNRES) {  // 32 rows per wave
+      const int l = opaque_lane();
+      copy_to_lds4_at(ex.rows_in + m0,
+                      (uint32_t)min(wave * 32 + (l >> 1), M - 1 - m0) * 8u + (uint32_t)(l & 1) * 4u,
+                      lds_address(&srow[tpar][wave * 32]));
+    }
+
+    Acc acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] = Acc{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // The tile's first stage: its W and j = 0 rows landed before the last
+    // barrier A.
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      read_x0(0, ks);
+      read_x0(1, ks);
+#pragma unroll
+      for (int i = 0; i < TI; ++i) read_w(i, ks);
+    }
+
+    for (int kt = 0; kt < nkt; ++kt) {
+      const bool last = kt == nkt - 1;
+      const uint32_t go = more();
+      // Phase j = 0: 16 steps of two MFMAs.
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int ks = q >> 3, i = q & 7;
+        acc[i][0] = mma(fw[i][ks], f0[0][ks], acc[i][0]);
+        acc[i][1] = mma(fw[i][ks], f0[1][ks], acc[i][1]);
+        if (q == 3) {
+          // Barrier B: the j = 1 rows of this stage have landed (at a tile's
+          // first stage they had before the previous epilogue's first
+          // store); W and the j = 0 rows are read out.  8 copies, or more,
+          // were issued after those waited for, unless the stream has ended.
+          if (kt > 0) {
+            if (go)
+              asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            else
+              asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          }
+          __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+          __syncthreads();
+        }
+        if (q >= 4 && q < 8) read_x1(q & 1, (q - 4) >> 1);
+        if (q >= 5 && (q & 1)) copy((q - 5) >> 1, p, go);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // Barrier A: W and the j = 0 rows of the next stage have landed (at a
+      // tile's first stage as above); the j = 1 rows are read out.  (A tile
+      // of one stage publishes its per-feature vectors here.)
+      if (kt > 0 || first || nkt == 1) {
+        if (go && nkt > 1)
+          asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      __syncthreads();
+      // The next stage is read from the other parity.
+      const uint32_t other = p ? 0u - BUF : BUF;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        aw[ks] += other;
+        ax[ks] += other;
+      }
+      const uint32_t go1 = lane_mask(go && !last);
+      __builtin_amdgcn_sched_barrier(0);
+      // Phase j = 1 (the fragments read at a tile's last stage are not used).
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int ks = q >> 3, i = q & 7;
+        acc[i][2] = mma(fw[i][ks], f1[0][ks], acc[i][2]);
+        acc[i][3] = mma(fw[i][ks], f1[1][ks], acc[i][3]);
+        read_w(i, ks);
+        if (i >= 6) read_x0(i - 6, ks);
+        if (q == 1 || q == 3) copy(6 + (q >> 1), p, go1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (go1) advance();
+      p ^= 1;
+    }
+    first = false;
+
+    // Region rows 0 .. 15 beside the stages, rows 16 .. 31 in this wave's
+    // copy slots of the j = 1 rows of the last stage's parity.
+    u32x4* const spare = smem + SPARE / 16 + wave * 128;
+    u32x4* const slots = smem + (X0 + (p ^ 1) * BUF + HALF) / 16 + wave * 64;
+    auto slot16 = [&](int r, int c) -> u32x4* {
+      return r < 16 ? spare + r * 8 + c : slots + (r < 24 ? 0 : 512) + (r & 7) * 8 + c;
+    };
+    auto vec = [&](int v, int q) { return svec[tpar][v][(wn0 >> 2) + q]; };
+    auto rows = [&](int r) {
+      if constexpr (FOLD || LNRES) return srow[tpar][wm0 + r];
+      return float2{0.0f, 0.0f};
+    };
+    store_tile<TJ, TI, EPI>(acc, slot16, vec, rows, R, Y, m0 + wm0, n0 + wn0, M, N, opaque_lane(), ex);
+
+    // The held-back copies, into slots only this wave has used since.
+    const uint32_t go = more();
+    copy(6, p ^ 1, go);
+    copy(7, p ^ 1, go);
+    if (go) advance();
+    tpar ^= 1;
+    t += G;
+    if (t >= n_tiles) break;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_linear_wide(const uint16_t* X, const uint16_t* W, const float* bias,
+                              const uint16_t* R, uint16_t* Y, int64_t M, int N, int K, int epi,
+                              const LinearExtra& ex, hipStream_t stream) {
+  if (2 * K >= 1 << 24) return hipErrorInvalidValue;  // copy offsets: 24-bit row strides
+  const int tiles_n = N / 256;
+  const int n_tiles = (int)((M + 255) / 256 * tiles_n);
+  const dim3 grid((unsigned)std::min(n_tiles, ex.n_cus)), block(512);
+#define SURGE_LAUNCH_EPI(E, O)                                                               \
+  hipLaunchKernelGGL((linear_wide_kernel<E, O>), grid, block, 0, stream, X, W, bias, R, Y, (int)M, \
+                     N, K, tiles_n, n_tiles, ex)
+  switch (epi) {
+    case EPI_BIAS: SURGE_LAUNCH_EPI(EPI_BIAS, ORDER_ROW_GROUPS); break;
+    case EPI_BIAS_GELU: SURGE_LAUNCH_EPI(EPI_BIAS_GELU, ORDER_FEATURE_HALVES); break;
+    case EPI_BIAS_RESIDUAL: SURGE_LAUNCH_EPI(EPI_BIAS_RESIDUAL, ORDER_ROW_GROUPS); break;
+    case EPI_FOLD: SURGE_LAUNCH_EPI(EPI_FOLD, ORDER_ROW_GROUPS); break;
+    case EPI_FOLD_GELU: SURGE_LAUNCH_EPI(EPI_FOLD_GELU, ORDER_FEATURE_HALVES); break;
+    case EPI_RES_STATS: SURGE_LAUNCH_EPI(EPI_RES_STATS, ORDER_ROW_GROUPS); break;
+    default: SURGE_LAUNCH_EPI(EPI_LNRES_STATS, ORDER_ROW_GROUPS); break;
+  }
+#undef SURGE_LAUNCH_EPI
+  return hipGetLastError();
+}
+
+}  // namespace surge
