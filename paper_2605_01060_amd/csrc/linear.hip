@@ -291,12 +291,13 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
   }
 }
 
+// The first `cols` of the N features.
 hipError_t launch_mid(const uint16_t* X, const uint16_t* W, const float* bias, const uint16_t* R,
-                      uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& ex,
-                      hipStream_t stream) {
+                      uint16_t* Y, int64_t M, int N, int cols, int K, int epi,
+                      const LinearExtra& ex, hipStream_t stream) {
   constexpr int BM = 128, BN = 128, PER_CU = 2;
   if ((int64_t)BM * K * 2 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;  // copy offsets
-  const int tiles_n = N / BN;
+  const int tiles_n = cols / BN;
   const int64_t tiles_m = (M + BM - 1) / BM;
   const int n_tiles = (int)(tiles_m * tiles_n);
   const dim3 grid((unsigned)std::min<int64_t>(n_tiles, (int64_t)ex.n_cus * PER_CU));
@@ -319,13 +320,7 @@ hipError_t launch_mid(const uint16_t* X, const uint16_t* W, const float* bias, c
 
 }  // namespace
 
-// The tile configuration of an [M, N] output: 256 x 256 tiles (8 waves of
-// 64 tokens x 128 features, one workgroup per CU) where the feature count
-// allows it and there are enough token rows to fill the chip; 128 x 128
-// tiles (4 waves of 64 x 64, two workgroups per CU) otherwise.
-static bool big_tiles(int64_t M, int N) { return N % 256 == 0 && M >= 8192; }
-
-// Below that, where a tile's own chain of latencies is the launch's time:
+// Small chunks, where a tile's own chain of latencies is the launch's time:
 // the smallest tile of which there is still at most one per CU.  A smaller
 // tile is a shorter chain (copies, barrier and MFMAs per stage) and spreads
 // the stream of W over more CUs; once there is more than one per CU the
@@ -340,6 +335,22 @@ static RingTile ring_tile(int64_t M, int N, int n_cus) {
   if (fits(64, 64)) return RING_64x64;
   if (fits(64, 128)) return RING_64x128;
   return RING_NONE;
+}
+
+// 256 x 256 tiles (one workgroup per CU) or 128 x 128 tiles (two): the family
+// whose rounds take less time.  The unit is a full round of 128-wide tiles.
+// Those fill the chip by halves of a round and end about 0.15 late; a round
+// of 256-wide tiles does twice the work in 1.5 + 134 / K units (the less, the
+// more main loop there is per epilogue), but a begun round costs a whole one.  Measured (us, 128 / 256 wide): N = 2304, K = 768:
+// M = 4096 21.3 / 21.1, 6144 26.9 / 23.6, 8192 33.1 / 41.6, 13,579 52.4 /
+// 47.3, 32,768 115 / 107; N = 768, K = 3072: 8192 45.5 / 65.8, 13,579 81.5 /
+// 69.5, 27,000 125 / 143; N = 1536, K = 384: 13,579 30.4 / 36.1, 32,768 58.5
+// / 56.4.
+static bool wide_is_faster(int64_t M, int N, int K, int n_cus) {
+  const int64_t t128 = (M + 127) / 128 * (N / 128), t256 = (M + 255) / 256 * (N / 256);
+  const double mid = 0.5 * (double)((t128 + n_cus - 1) / n_cus) + 0.15;
+  const double wide = (1.5 + 134.0 / K) * (double)((t256 + n_cus - 1) / n_cus);
+  return wide <= mid;
 }
 
 int linear_stats_width(int64_t, int) { return STATS_WIDTH; }
@@ -363,9 +374,25 @@ hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias
   const RingTile tile = ring_tile(M, N, ex.n_cus);
   if (tile != RING_NONE)
     return launch_linear_ring(tile, X, W, bias, R, Y, M, N, K, epi, ex, stream);
-  if (big_tiles(M, N))
-    return launch_linear_wide(X, W, bias, R, Y, M, N, K, epi, ex, stream);
-  return launch_mid(X, W, bias, R, Y, M, N, K, epi, ex, stream);
+  // N is a multiple of 128.  An odd one takes 256-wide tiles over all but its
+  // last 128 features where that is most of them and the launch is long: the
+  // rest reads X once more in a launch of its own (N = 1152, K = 384: 311 ->
+  // 276 us at 265,000 rows, 115 -> 118 at 100,000; N = 384, K = 1536: 406 ->
+  // 470 at 265,000).
+  const int cols = N & ~255;
+  const bool split = cols < N;
+  const int64_t t256 = (M + 255) / 256 * (cols / 256);
+  if (split ? cols < 1024 || t256 < 8 * (int64_t)ex.n_cus : !wide_is_faster(M, N, K, ex.n_cus))
+    return launch_mid(X, W, bias, R, Y, M, N, N, K, epi, ex, stream);
+  hipError_t e = launch_linear_wide(X, W, bias, R, Y, M, N, K, epi, ex, stream);
+  if (e != hipSuccess || !split) return e;
+  LinearExtra rest = ex;
+  if (ex.stats_out) rest.stats_out = ex.stats_out + (int64_t)(cols / STATS_WIDTH) * M;
+  if (ex.col_s) rest.col_s = ex.col_s + cols;
+  if (ex.gamma) rest.gamma = ex.gamma + cols;
+  if (ex.beta) rest.beta = ex.beta + cols;
+  return launch_mid(X, W + (int64_t)cols * K, bias + cols, R ? R + cols : nullptr, Y + cols, M, N,
+                    N - cols, K, epi, rest, stream);
 }
 
 }  // namespace surge

@@ -413,3 +413,39 @@ def test_small_calls_match_the_large_call_bit_for_bit(N, K, epi):
         ys, ss = call(rows)
         assert torch.equal(ys, y[:rows]), rows
         assert torch.equal(ss, st[:, :rows]), rows
+
+
+@pytest.mark.parametrize("N,epi", [(1152, 3), (1152, 6), (1024, 4), (768, 5)])
+def test_tile_families_match_bit_for_bit(N, epi):
+    """256-wide tiles (for N = 1152 with a last 128 features of 128-wide ones)
+    against 128-wide tiles of the same rows, in chunks of 5,000: outputs and
+    statistics are equal, ragged last rows included."""
+    torch = torch_cuda()
+    K = 128
+    g = torch.Generator(device="cuda").manual_seed(N + epi)
+    M = 8 * 256 * 256 // (N // 256) + 77
+
+    def randn(*dims):
+        return torch.randn(dims, generator=g, device="cuda")
+
+    x, w, b = randn(M, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
+    res = randn(M, N).bfloat16() if epi in (5, 6) else None
+    raw = (res if epi == 6 else x).float().view(M, -1, 64)
+    st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)
+    vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N))
+
+    def call(a, e):
+        y = torch.empty((e - a, N), dtype=torch.bfloat16, device="cuda")
+        st = torch.zeros((N // 64, e - a, 2), device="cuda")
+        S.surge_op_linear_ln(e - a, N, K, x[a:e], w, b, None if res is None else res[a:e], epi,
+                             st_in[a:e].transpose(0, 1).contiguous(), st_in.shape[1], *vecs, 1e-12,
+                             st, y)
+        return y, st
+
+    y, st = call(0, M)
+    for a in (0, M // 2 // 8 * 8, M - 5000 + M % 8):
+        ys, ss = call(a, a + min(5000, M - a))
+        n = ys.shape[0]
+        assert torch.equal(ys, y[a:a + n]), a
+        if epi >= 5:
+            assert torch.equal(ss, st[:, a:a + n]), a
