@@ -218,10 +218,10 @@ surge_status encode_chunks(surge_encoder* e, int64_t n_texts, const int32_t* d_t
     // In a small chunk the GEMMs merge the partials themselves (QKV and
     // O-projection those of X, FFN1 and FFN2 those of Y) and the row-factor
     // kernel does not run, but for the pooling after the last layer.
-    const bool merge_x = linear_merges_stats(T, 3 * d, parts, e->n_cus) &&
-                         linear_merges_stats(T, d, parts, e->n_cus);
-    const bool merge_y = linear_merges_stats(T, f, parts, e->n_cus) &&
-                         linear_merges_stats(T, d, parts, e->n_cus);
+    const bool merge_x = linear_merges_stats(T, 3 * d, d, parts, e->n_cus) &&
+                         linear_merges_stats(T, d, d, parts, e->n_cus);
+    const bool merge_y = linear_merges_stats(T, f, d, parts, e->n_cus) &&
+                         linear_merges_stats(T, d, f, parts, e->n_cus);
     LinearExtra from_x, from_y;  // where the factors of X's and Y's rows come from
     from_x.n_cus = from_y.n_cus = e->n_cus;
     from_x.rows_in = merge_x ? nullptr : e->RX;

@@ -75,7 +75,11 @@ __device__ __forceinline__ void wait_copies(int later) {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CPS) : "memory");
 }
 
-template <int EPI, int ORDER>
+// With MERGE the rows' LayerNorm factors come from the statistics partials
+// (ex.stats_in): lane r of a wave loads those of the wave's row r at the
+// tile's start, so that their latency hides behind the main loop, and merges
+// them before the epilogue.  Otherwise the lane loads the row's factors.
+template <int EPI, int ORDER, bool MERGE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
                         const float* __restrict__ bias, const uint16_t* __restrict__ R,
@@ -216,13 +220,18 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
       copy_lanes_to_lds16(src + n0, lds_address(&svec[tpar][wave][0]));
     }
 
-    // LayerNorm factors of this lane's rows (fused LayerNorm epilogues),
-    // fetched now so their latency hides behind the main loop.
-    float2 rowf[TJ];
+    // LayerNorm factors of the wave's row `lane` (fused LayerNorm epilogues).
+    constexpr int MAXP = MERGE ? RING_MAX_PARTS : 1;
+    float2 rowf[MAXP];
+    if constexpr (FOLD_ || LNRES_) {
+      const int m = min(m0 + wm0 + lane, M - 1);
+      if constexpr (MERGE) {
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      rowf[j] = make_float2(0.0f, 0.0f);
-      if constexpr (FOLD_ || LNRES_) rowf[j] = ex.rows_in[min(m0 + wm0 + j * 16 + l16, M - 1)];
+        for (int q = 0; q < MAXP; ++q)
+          if (q < ex.parts_in) rowf[q] = ex.stats_in[(size_t)q * M + m];
+      } else {
+        rowf[0] = ex.rows_in[m];
+      }
     }
 
     Acc acc[TI][TJ];
@@ -278,7 +287,15 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
       return rbase + (r >> 3) * (NWAVES * 64) + (r & 7) * 8 + c;
     };
     auto vec = [&](int v, int q) { return svec[tpar][v][(wn0 >> 2) + q]; };
-    auto rows = [&](int r) { return rowf[r >> 4]; };  // row r = 16 j + lane % 16
+    float2 own = make_float2(0.0f, 0.0f);
+    if constexpr (FOLD_ || LNRES_) {
+      own = rowf[0];
+      if constexpr (MERGE)
+        own = ln_row_factors<MAXP>([&](int q) { return rowf[q]; }, ex.parts_in, ex.eps);
+    }
+    auto rows = [&](int r) {
+      return make_float2(__shfl(own.x, r, 64), __shfl(own.y, r, 64));
+    };
     store_tile<TJ, TI, EPI>(acc, slot16, vec, rows, R, Y, m0 + wm0, n0 + wn0, M, N, lane, ex);
 
     // The region's reads are done (waited above); this wave's deferred copies
@@ -302,9 +319,14 @@ hipError_t launch_mid(const uint16_t* X, const uint16_t* W, const float* bias, c
   const int n_tiles = (int)(tiles_m * tiles_n);
   const dim3 grid((unsigned)std::min<int64_t>(n_tiles, (int64_t)ex.n_cus * PER_CU));
   const dim3 block(256);
-#define SURGE_LAUNCH_EPI(E, O)                                                                   \
-  hipLaunchKernelGGL((linear_bf16_kernel<E, O>), grid, block, 0, stream, X, W, bias, R, Y, (int)M, \
-                     N, K, tiles_n, n_tiles, ex)
+  const bool merge = !ex.rows_in;
+#define SURGE_LAUNCH_EPI(E, O)                                                                  \
+  if (merge && (E == EPI_FOLD || E == EPI_FOLD_GELU || E == EPI_LNRES_STATS))                   \
+    hipLaunchKernelGGL((linear_bf16_kernel<E, O, true>), grid, block, 0, stream, X, W, bias, R, \
+                       Y, (int)M, N, K, tiles_n, n_tiles, ex);                                  \
+  else                                                                                          \
+    hipLaunchKernelGGL((linear_bf16_kernel<E, O, false>), grid, block, 0, stream, X, W, bias,   \
+                       R, Y, (int)M, N, K, tiles_n, n_tiles, ex)
   switch (epi) {
     case EPI_BIAS: SURGE_LAUNCH_EPI(EPI_BIAS, ORDER_ROW_GROUPS); break;
     case EPI_BIAS_GELU: SURGE_LAUNCH_EPI(EPI_BIAS_GELU, ORDER_FEATURE_HALVES); break;
@@ -363,29 +385,48 @@ hipError_t resolve_cus(int* n_cus) {
   return hipDeviceGetAttribute(n_cus, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
-bool linear_merges_stats(int64_t M, int N, int parts, int n_cus) {
-  return parts <= RING_MAX_PARTS && ring_tile(M, N, n_cus) != RING_NONE;
+// Which family a launch takes.  N is a multiple of 128: an odd one takes
+// 256-wide tiles over all but its last 128 features where that is most of
+// them and the launch is long: the rest reads X once more in a launch of its
+// own (N = 1152, K = 384: 311 -> 276 us at 265,000 rows, 115 -> 118 at
+// 100,000; N = 384, K = 1536: 406 -> 470 at 265,000).
+enum Family { FAMILY_RING, FAMILY_MID, FAMILY_WIDE, FAMILY_WIDE_AND_MID };
+static Family linear_family(int64_t M, int N, int K, int n_cus) {
+  if (ring_tile(M, N, n_cus) != RING_NONE) return FAMILY_RING;
+  const int64_t t256 = (M + 255) / 256 * (N / 256);
+  if (N % 256 == 0) return wide_is_faster(M, N, K, n_cus) ? FAMILY_WIDE : FAMILY_MID;
+  return N > 1024 && t256 >= 8 * (int64_t)n_cus ? FAMILY_WIDE_AND_MID : FAMILY_MID;
+}
+
+// The tiles merge statistics where that costs less than a row-factor launch
+// (5 us with its gap): always in small chunks; 128-wide tiles hide the loads
+// but repeat them for every feature tile, up to four rounds; 256-wide tiles
+// have no registers to hold them over a main loop and merge before it, in
+// launches of one tile per workgroup.
+bool linear_merges_stats(int64_t M, int N, int K, int parts, int n_cus) {
+  if (parts > RING_MAX_PARTS) return false;
+  switch (linear_family(M, N, K, n_cus)) {
+    case FAMILY_RING: return true;
+    case FAMILY_MID: return (M + 127) / 128 * (N / 128) <= 8 * (int64_t)n_cus;
+    case FAMILY_WIDE: return (M + 255) / 256 * (N / 256) <= n_cus;
+    default: return false;
+  }
 }
 
 hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias, const uint16_t* R,
                          uint16_t* Y, int64_t M, int N, int K, int epi, const LinearExtra& ex,
                          hipStream_t stream) {
   if (M <= 0) return hipSuccess;
-  const RingTile tile = ring_tile(M, N, ex.n_cus);
-  if (tile != RING_NONE)
-    return launch_linear_ring(tile, X, W, bias, R, Y, M, N, K, epi, ex, stream);
-  // N is a multiple of 128.  An odd one takes 256-wide tiles over all but its
-  // last 128 features where that is most of them and the launch is long: the
-  // rest reads X once more in a launch of its own (N = 1152, K = 384: 311 ->
-  // 276 us at 265,000 rows, 115 -> 118 at 100,000; N = 384, K = 1536: 406 ->
-  // 470 at 265,000).
-  const int cols = N & ~255;
-  const bool split = cols < N;
-  const int64_t t256 = (M + 255) / 256 * (cols / 256);
-  if (split ? cols < 1024 || t256 < 8 * (int64_t)ex.n_cus : !wide_is_faster(M, N, K, ex.n_cus))
-    return launch_mid(X, W, bias, R, Y, M, N, N, K, epi, ex, stream);
+  const bool factors = epi == EPI_FOLD || epi == EPI_FOLD_GELU || epi == EPI_LNRES_STATS;
+  if (factors && !ex.rows_in && !linear_merges_stats(M, N, K, ex.parts_in, ex.n_cus))
+    return hipErrorInvalidValue;
+  const Family family = linear_family(M, N, K, ex.n_cus);
+  if (family == FAMILY_RING)
+    return launch_linear_ring(ring_tile(M, N, ex.n_cus), X, W, bias, R, Y, M, N, K, epi, ex, stream);
+  if (family == FAMILY_MID) return launch_mid(X, W, bias, R, Y, M, N, N, K, epi, ex, stream);
   hipError_t e = launch_linear_wide(X, W, bias, R, Y, M, N, K, epi, ex, stream);
-  if (e != hipSuccess || !split) return e;
+  if (e != hipSuccess || family == FAMILY_WIDE) return e;
+  const int cols = N & ~255;
   LinearExtra rest = ex;
   if (ex.stats_out) rest.stats_out = ex.stats_out + (int64_t)(cols / STATS_WIDTH) * M;
   if (ex.col_s) rest.col_s = ex.col_s + cols;

@@ -134,6 +134,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 
   int t = blockIdx.x;  // < n_tiles: the grid is never larger than the tile count
   point();
+  // Without row factors the launch has one tile per workgroup: lane r merges
+  // the statistics of its wave's row r, before the first copy (a wait for
+  // the loads is then no wait for copies).
+  if constexpr (FOLD || LNRES) {
+    if (!ex.rows_in) {
+      int tm, tn;
+      tile_coords<ORDER>(t, n_tiles, tiles_n, &tm, &tn);
+      const int m = min(tm * BM + wm0 + lane, M - 1);
+      srow[0][wm0 + lane] = ln_row_factors<RING_MAX_PARTS>(
+          [&](int q) { return ex.stats_in[(size_t)q * M + m]; }, ex.parts_in, ex.eps);
+    }
+  }
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const uint32_t go = more();
@@ -168,9 +180,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     }
     if constexpr (FOLD || LNRES) {  // 32 rows per wave
       const int l = opaque_lane();
-      copy_to_lds4_at(ex.rows_in + m0,
-                      (uint32_t)min(wave * 32 + (l >> 1), M - 1 - m0) * 8u + (uint32_t)(l & 1) * 4u,
-                      lds_address(&srow[tpar][wave * 32]));
+      if (ex.rows_in)
+        copy_to_lds4_at(ex.rows_in + m0,
+                        (uint32_t)min(wave * 32 + (l >> 1), M - 1 - m0) * 8u + (uint32_t)(l & 1) * 4u,
+                        lds_address(&srow[tpar][wave * 32]));
     }
 
     Acc acc[TI][TJ];
@@ -282,6 +295,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 hipError_t launch_linear_wide(const uint16_t* X, const uint16_t* W, const float* bias,
                               const uint16_t* R, uint16_t* Y, int64_t M, int N, int K, int epi,
                               const LinearExtra& ex, hipStream_t stream) {
+  const bool factors = epi == EPI_FOLD || epi == EPI_FOLD_GELU || epi == EPI_LNRES_STATS;
+  if (factors && !ex.rows_in && (ex.parts_in > RING_MAX_PARTS || (M + 255) / 256 * (N / 256) > ex.n_cus))
+    return hipErrorInvalidValue;
   if (2 * K >= 1 << 24) return hipErrorInvalidValue;  // copy offsets: 24-bit row strides
   const int tiles_n = N / 256;
   const int n_tiles = (int)((M + 255) / 256 * tiles_n);

@@ -241,7 +241,7 @@ surge_status surge_op_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t*
   int n_cus = 0;
   HIP_TRY(resolve_cus(&n_cus));
   DeviceBuf rows;  // per-row LayerNorm factors, freed on return
-  if (factors && !linear_merges_stats(M, N, parts_in, n_cus)) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
+  if (factors && !linear_merges_stats(M, N, K, parts_in, n_cus)) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
   st = enqueue_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in, parts_in, d_col_s,
                          d_gamma, d_beta, eps, d_stats_out, d_y, (float2*)rows.ptr, n_cus, s);
   if (st != SURGE_OK) return st;
@@ -268,7 +268,7 @@ surge_status surge_op_linear_ln_noalloc(int64_t M, int32_t N, int32_t K, const u
                 (long long)M, (long long)kScratchRows);
   int n_cus = 0;
   HIP_TRY(resolve_cus(&n_cus));
-  if (factors && !linear_merges_stats(M, N, parts_in, n_cus)) {
+  if (factors && !linear_merges_stats(M, N, K, parts_in, n_cus)) {
     st = scratch_address(&rows);
     if (st != SURGE_OK) return st;
   }
