@@ -5,8 +5,8 @@
 //
 // Three tile families share the operand layout, the K order and the finish
 // of every output, and launch_linear picks one by the launch's tile counts:
-// small chunks (linear_ring.hip), 256 x 256 tiles (linear_wide.hip), and the
-// 128 x 128 tiles of this file in between and for N not a multiple of 256.
+// small chunks (linear_ring.hip), 256 x 256 or 192 x 256 tiles
+// (linear_wide.hip), and the 128 x 128 tiles of this file in between and for N not a multiple of 256.
 //
 // Tiling.  A workgroup computes 128 x 128 tiles of Y (tokens x features) with
 // four waves of 64 x 64 (16x16x32 bf16 MFMAs).  K is walked in 64-wide stages
@@ -359,20 +359,27 @@ static RingTile ring_tile(int64_t M, int N, int n_cus) {
   return RING_NONE;
 }
 
-// 256 x 256 tiles (one workgroup per CU) or 128 x 128 tiles (two): the family
-// whose rounds take less time.  The unit is a full round of 128-wide tiles.
-// Those fill the chip by halves of a round and end about 0.15 late; a round
-// of 256-wide tiles does twice the work in 1.5 + 134 / K units (the less, the
-// more main loop there is per epilogue), but a begun round costs a whole one.  Measured (us, 128 / 256 wide): N = 2304, K = 768:
-// M = 4096 21.3 / 21.1, 6144 26.9 / 23.6, 8192 33.1 / 41.6, 13,579 52.4 /
-// 47.3, 32,768 115 / 107; N = 768, K = 3072: 8192 45.5 / 65.8, 13,579 81.5 /
-// 69.5, 27,000 125 / 143; N = 1536, K = 384: 13,579 30.4 / 36.1, 32,768 58.5
-// / 56.4.
-static bool wide_is_faster(int64_t M, int N, int K, int n_cus) {
-  const int64_t t128 = (M + 127) / 128 * (N / 128), t256 = (M + 255) / 256 * (N / 256);
-  const double mid = 0.5 * (double)((t128 + n_cus - 1) / n_cus) + 0.15;
-  const double wide = (1.5 + 134.0 / K) * (double)((t256 + n_cus - 1) / n_cus);
-  return wide <= mid;
+// 256 x 256 or 192 x 256 tiles (one workgroup per CU), or 128 x 128 tiles
+// (two): the rows of the tile whose rounds take least.  The unit is a full
+// round of 128-wide tiles.  Those fill the chip by halves of a round and end
+// about 0.15 late; a round of 256-row tiles does twice the work in 1.5 + 134
+// / K units (the less, the more main loop there is per epilogue), and one of
+// 192-row tiles three quarters of that in 0.88 of the time (fewer MFMAs per
+// operand byte), but a begun round costs a whole one.  Measured (us, 128 /
+// 192 / 256): N = 2304, K = 768: M = 6144 28.8 / 39.5 / 25.0, 8192 34.6 /
+// 37.8 / 45.5, 10,000 42.3 / 38.6 / 43.9, 13,579 54.8 / 56.6 / 48.6; N = 768,
+// K = 3072: 8192 46.8 / 58.7 / 66.9, 13,579 81.8 / 66.8 / 74.1, 17,000 94.3 /
+// 122 / 73.6, 262,144 1,347 / 1,166 / 1,071.
+static int tile_rows(int64_t M, int N, int K, int n_cus) {
+  auto rounds = [&](int64_t bm, int bn) {
+    return (double)(((M + bm - 1) / bm * (N / bn) + n_cus - 1) / n_cus);
+  };
+  const double wide = 1.5 + 134.0 / K;
+  const double c128 = 0.5 * rounds(128, 128) + 0.15;
+  const double c192 = 0.88 * wide * rounds(192, 256);
+  const double c256 = wide * rounds(256, 256);
+  if (c192 < c256 && c192 < c128) return 192;
+  return c256 <= c128 ? 256 : 128;
 }
 
 int linear_stats_width(int64_t, int) { return STATS_WIDTH; }
@@ -391,11 +398,18 @@ hipError_t resolve_cus(int* n_cus) {
 // own (N = 1152, K = 384: 311 -> 276 us at 265,000 rows, 115 -> 118 at
 // 100,000; N = 384, K = 1536: 406 -> 470 at 265,000).
 enum Family { FAMILY_RING, FAMILY_MID, FAMILY_WIDE, FAMILY_WIDE_AND_MID };
-static Family linear_family(int64_t M, int N, int K, int n_cus) {
-  if (ring_tile(M, N, n_cus) != RING_NONE) return FAMILY_RING;
+struct Choice {
+  Family family;
+  int rows;  // of a wide tile
+};
+static Choice linear_family(int64_t M, int N, int K, int n_cus) {
+  if (ring_tile(M, N, n_cus) != RING_NONE) return {FAMILY_RING, 0};
+  if (N % 256 == 0) {
+    const int rows = tile_rows(M, N, K, n_cus);
+    return {rows == 128 ? FAMILY_MID : FAMILY_WIDE, rows};
+  }
   const int64_t t256 = (M + 255) / 256 * (N / 256);
-  if (N % 256 == 0) return wide_is_faster(M, N, K, n_cus) ? FAMILY_WIDE : FAMILY_MID;
-  return N > 1024 && t256 >= 8 * (int64_t)n_cus ? FAMILY_WIDE_AND_MID : FAMILY_MID;
+  return {N > 1024 && t256 >= 8 * (int64_t)n_cus ? FAMILY_WIDE_AND_MID : FAMILY_MID, 256};
 }
 
 // The tiles merge statistics where that costs less than a row-factor launch
@@ -405,10 +419,11 @@ static Family linear_family(int64_t M, int N, int K, int n_cus) {
 // launches of one tile per workgroup.
 bool linear_merges_stats(int64_t M, int N, int K, int parts, int n_cus) {
   if (parts > RING_MAX_PARTS) return false;
-  switch (linear_family(M, N, K, n_cus)) {
+  const Choice c = linear_family(M, N, K, n_cus);
+  switch (c.family) {
     case FAMILY_RING: return true;
     case FAMILY_MID: return (M + 127) / 128 * (N / 128) <= 8 * (int64_t)n_cus;
-    case FAMILY_WIDE: return (M + 255) / 256 * (N / 256) <= n_cus;
+    case FAMILY_WIDE: return (M + c.rows - 1) / c.rows * (N / 256) <= n_cus;
     default: return false;
   }
 }
@@ -420,11 +435,11 @@ hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias
   const bool factors = epi == EPI_FOLD || epi == EPI_FOLD_GELU || epi == EPI_LNRES_STATS;
   if (factors && !ex.rows_in && !linear_merges_stats(M, N, K, ex.parts_in, ex.n_cus))
     return hipErrorInvalidValue;
-  const Family family = linear_family(M, N, K, ex.n_cus);
+  const auto [family, rows] = linear_family(M, N, K, ex.n_cus);
   if (family == FAMILY_RING)
     return launch_linear_ring(ring_tile(M, N, ex.n_cus), X, W, bias, R, Y, M, N, K, epi, ex, stream);
   if (family == FAMILY_MID) return launch_mid(X, W, bias, R, Y, M, N, N, K, epi, ex, stream);
-  hipError_t e = launch_linear_wide(X, W, bias, R, Y, M, N, K, epi, ex, stream);
+  hipError_t e = launch_linear_wide(rows, X, W, bias, R, Y, M, N, K, epi, ex, stream);
   if (e != hipSuccess || family == FAMILY_WIDE) return e;
   const int cols = N & ~255;
   LinearExtra rest = ex;

@@ -265,8 +265,9 @@ hipError_t launch_linear_ring(RingTile tile, const uint16_t* X, const uint16_t* 
                               const float* bias, const uint16_t* R, uint16_t* Y, int64_t M, int N,
                               int K, int epi, const LinearExtra& ex, hipStream_t stream);
 
-// 256 x 256 tiles (linear_wide.hip) over the first N / 256 * 256 features.
-hipError_t launch_linear_wide(const uint16_t* X, const uint16_t* W, const float* bias,
+// rows x 256 tiles, rows 256 or 192 (linear_wide.hip), over the first
+// N / 256 * 256 features.
+hipError_t launch_linear_wide(int rows, const uint16_t* X, const uint16_t* W, const float* bias,
                               const uint16_t* R, uint16_t* Y, int64_t M, int N, int K, int epi,
                               const LinearExtra& ex, hipStream_t stream);
 

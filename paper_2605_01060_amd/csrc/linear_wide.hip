@@ -1,6 +1,7 @@
 // Token-major linear layers of large chunks (gfx950): Y = epi(X W^T + b) in
-// 256 x 256 tiles, one persistent 8-wave workgroup per CU, each wave a 64
-// token x 128 feature sub-tile of 16x16x32 bf16 MFMAs.
+// 256 x 256 tiles (192 x 256 where those leave fewer CUs idle), one persistent
+// 8-wave workgroup per CU, each wave a 64 token x 128 feature (96 x 64)
+// sub-tile of 16x16x32 bf16 MFMAs.
 //
 // What bounds it: the power limit and late operand copies.  On normal data
 // (K = 3072, TFLOP/s) a loop that gave each copy one K stage to arrive ran at
@@ -10,22 +11,21 @@
 // copies more time.  128 KB of LDS hold two 64-wide stages of a tile whatever
 // the schedule, so this one frees LDS earlier: a wave keeps a whole stage's W
 // fragments in registers;
-// a stage runs as two phases, token half j = 0 then j = 1 of the wave's rows
-// against the same 16 W fragments, and each W fragment is replaced by the
+// a stage runs as two phases, the wave's first and then its other token rows
+// against the same W fragments, and each W fragment is replaced by the
 // next stage's right after its last MFMA.  So
-//   - W and the j = 0 rows of stage s are read out by the end of stage s-1,
+//   - W and the phase-0 rows of stage s are read out by the end of stage s-1,
 //     and their LDS takes stage s+2 from there on (barrier B, placed after
 //     the first four MFMAs of stage s so that no wave waits for its reads);
-//   - the j = 1 rows of stage s are read out by the middle of stage s
+//   - the phase-1 rows of stage s are read out by the middle of stage s
 //     (barrier A, between the phases), and theirs takes stage s+2.
 // Every copy has one and a half stages to arrive, and the MFMAs after either
 // barrier find their operands in registers.  The copies are spread over the
 // MFMAs, since a burst of them blocks the issue of everything behind it.
 //
-// The copy stream runs on across tile boundaries.  Only the j = 1 rows of
-// the next tile's second stage are held back: their LDS (8 of the 16 KB of a
-// wave's copy slots) and 16 KB beside the stages are the waves' epilogue
-// regions.  The accumulators see the same K order as every other tile shape.
+// The copy stream runs on across tile boundaries.  Only the phase-1 rows of
+// the next tile's second stage are held back: their LDS and 16 KB (24 KB)
+// beside the stages are the waves' epilogue regions.  The accumulators see the same K order as every other tile shape.
 //
 // Measured against the loop of one-stage tolerance on 32x32x16 MFMAs that it
 // replaces (M = 262,144, us): QKV 898 -> 828, FFN2 1,132 -> 1,061, FFN1
@@ -41,54 +41,67 @@ __device__ __forceinline__ bf16x8 lds_fragment(uint32_t addr) {
   return __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4*)addr);
 }
 
-template <int EPI, int ORDER>
+// WAVES_M x WAVES_N waves of 16 (J0 + J1) tokens x 16 TI features; phase 0
+// takes J0 of a wave's token fragments, phase 1 the other J1.
+template <int WAVES_M, int WAVES_N, int TI, int J0, int J1, int EPI, int ORDER>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void linear_wide_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, const float* __restrict__ bias,
     const uint16_t* __restrict__ R, uint16_t* __restrict__ Y, int M, int N, int K, int tiles_n,
     int n_tiles, LinearExtra ex) {
-  constexpr int BM = 256, BN = 256, TI = 8, TJ = 4;
-  // LDS, in bytes from smem: W of stage parity p at p * BUF; the j rows of X
-  // at X0 + p * BUF + j * HALF; the spare halves of the epilogue regions.
-  constexpr uint32_t BUF = 32768, HALF = 16384, X0 = 65536, SPARE = 131072;
+  constexpr int TJ = J0 + J1;
+  constexpr int R0 = 16 * J0, R1 = 16 * J1;  // a wave's token rows of either phase
+  constexpr int BM = WAVES_M * (R0 + R1), BN = 256;
+  constexpr int C1 = WAVES_M * R1 / 64;      // copies per wave of the phase-1 rows
+  constexpr int CPS = 6 + C1;                // ... of a stage: 4 W, 2 phase-0 rows, C1
+  static_assert(WAVES_M * WAVES_N == 8 && WAVES_N * TI == 16 && WAVES_M * R0 == 128 &&
+                    WAVES_M * R1 == 64 * C1 && C1 <= 2 && J1 == 2 && TI * J0 == 16,
+                "tiles of this kernel");
+  // LDS, in bytes from smem: a stage of parity p at p * BUF, its W rows, then
+  // (X0 on) its phase-0 and (X1 on) phase-1 rows of X, wave_m by wave_m; the
+  // spare parts of the epilogue regions, 32 rows less the 8 C1 in copy slots.
+  constexpr uint32_t X0 = 32768, X1 = X0 + 16384, BUF = X1 + C1 * 8192, SPARE = 2 * BUF;
+  constexpr int SPARE_ROWS = 32 - 8 * C1;
   constexpr bool FOLD = EPI == EPI_FOLD || EPI == EPI_FOLD_GELU;
   constexpr bool LNRES = EPI == EPI_LNRES_STATS;
   constexpr int NV = 1 + (FOLD ? 1 : 0) + (LNRES ? 2 : 0);
-  __shared__ u32x4 smem[(SPARE + HALF) / 16];
+  __shared__ u32x4 smem[SPARE / 16 + 8 * SPARE_ROWS * 8];
   // Per-feature vectors (bias, then col_s or gamma and beta) by tile parity.
   __shared__ float4 svec[2][NV][BN / 4];
-  __shared__ float2 srow[2][FOLD || LNRES ? BM : 1];  // LayerNorm factors of the tile's rows
+  __shared__ float2 srow[2][FOLD || LNRES ? 256 : 1];  // LayerNorm factors of the tile's rows
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wave_m = wave >> 1;
-  const int wn0 = (wave & 1) * 128;
-  const int wm0 = wave_m * 64;
+  const int wave_m = wave / WAVES_N;
+  const int wn0 = (wave % WAVES_N) * (16 * TI);
+  const int wm0 = wave_m * (R0 + R1);
   const int nkt = K / 64;
   const int G = gridDim.x;
 
   // Fragment addresses of stage parity 0: row lane % 16, then the swizzled
   // 16-byte chunk of the 32-wide K step ks; fragments are 16 rows apart.
   const uint32_t lds = lds_address(smem);
-  uint32_t aw[2], ax[2];
+  uint32_t aw[2], ax[2], ax1[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     const uint32_t ch = (uint32_t)swz<8>(lane & 15, ks * 4 + (lane >> 4)) * 16u;
     aw[ks] = lds + (uint32_t)wn0 * 128u + ch;
-    ax[ks] = lds + X0 + (uint32_t)wave_m * 4096u + ch;
+    ax[ks] = lds + X0 + (uint32_t)(wave_m * R0) * 128u + ch;
+    ax1[ks] = lds + X1 + (uint32_t)(wave_m * R1) * 128u + ch;
   }
-  bf16x8 fw[TI][2], f0[2][2], f1[2][2];  // W; the j = 0 and j = 1 rows
+  bf16x8 fw[TI][2], f0[J0][2], f1[J1][2];
   auto read_w = [&](int i, int ks) { fw[i][ks] = lds_fragment(aw[ks] + i * 2048); };
-  auto read_x0 = [&](int jj, int ks) { f0[jj][ks] = lds_fragment(ax[ks] + jj * 2048); };
-  auto read_x1 = [&](int jj, int ks) { f1[jj][ks] = lds_fragment(ax[ks] + HALF + jj * 2048); };
+  auto read_x0 = [&](int j, int ks) { f0[j][ks] = lds_fragment(ax[ks] + j * 2048); };
+  auto read_x1 = [&](int j, int ks) {  // (J0 == J1: the same rows, X1 - X0 on)
+    f1[j][ks] = lds_fragment((J0 == J1 ? ax[ks] + (X1 - X0) : ax1[ks]) + j * 2048);
+  };
 
-  // Copies.  A wave instruction fills 8 rows of 128 bytes; the 32 rows of
-  // wave_m in half j of X are tile rows wave_m * 64 + j * 32 + 0 .. 31.
+  // Copies.  A wave instruction fills 8 rows of 128 bytes.
   const uint32_t ldsw = __builtin_amdgcn_readfirstlane(lds + wave * 1024);
   int it_tile = blockIdx.x;  // the copy stream's tile and stage
   int it_kt = 0;
   const uint16_t* xs;
   const uint16_t* ws;
-  uint32_t xo[4];
+  uint32_t xo[2 + C1];
   const uint32_t wo = __umul24((uint32_t)(wave * 8 + (lane >> 3)), (uint32_t)K * 2u) +
                       (uint32_t)copy_chunk<8>(lane, wave) * 16u;
   // A copy of the lane index that the compiler cannot see through: what is
@@ -105,23 +118,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     xs = X + (size_t)(tm_ * BM) * K;
     ws = W + (size_t)(tn_ * BN) * K;
     const int l = opaque_lane();
-    const int lr = wave * 8 + (l >> 3);
-    const int row0 = (lr >> 5) * 64 + (lr & 31);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {  // half q / 2, copy q % 2; rows past M: clamped
-      const int row = min(row0 + (q >> 1) * 32 + (q & 1) * 128, M - 1 - tm_ * BM);
-      xo[q] = __umul24((uint32_t)row, (uint32_t)K * 2u) + (uint32_t)copy_chunk<8>(l, wave) * 16u;
+    for (int q = 0; q < 2 + C1; ++q) {  // copies 0, 1: phase 0; rows past M: clamped
+      const int lr = (q & 1) * 64 + wave * 8 + (l >> 3);
+      const int row = q < 2 ? lr / R0 * (R0 + R1) + lr % R0 : lr / R1 * (R0 + R1) + R0 + lr % R1;
+      xo[q] = __umul24((uint32_t)min(row, M - 1 - tm_ * BM), (uint32_t)K * 2u) +
+              (uint32_t)copy_chunk<8>(l, wave) * 16u;
     }
   };
   // Copy c of the cursor's stage into parity p, skipped where `go` is 0:
-  // 0 .. 3 W, 4 .. 5 the j = 0 rows, 6 .. 7 the j = 1 rows.
+  // 0 .. 3 W, 4 .. 5 the phase-0 rows, 6 on the phase-1 rows.
   auto copy = [&](int c, uint32_t p, uint32_t go) {
     const uint32_t base = ldsw + p * BUF;
     if (c < 4)
       copy_to_lds16_if(ws + (size_t)(c * 64) * K + it_kt * 64, wo, base + c * 8192, go);
     else
-      copy_to_lds16_if(xs + it_kt * 64, xo[c - 4],
-                       base + X0 + ((c - 4) >> 1) * HALF + ((c - 4) & 1) * 8192, go);
+      copy_to_lds16_if(xs + it_kt * 64, xo[c - 4], base + X0 + (c - 4) * 8192, go);
   };
   auto advance = [&]() {
     if (++it_kt == nkt) {
@@ -134,15 +146,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 
   int t = blockIdx.x;  // < n_tiles: the grid is never larger than the tile count
   point();
-  // Without row factors the launch has one tile per workgroup: lane r merges
-  // the statistics of its wave's row r, before the first copy (a wait for
-  // the loads is then no wait for copies).
+  // Without row factors the launch has one tile per workgroup: thread r
+  // merges the statistics of row r, before the first copy (a wait for the
+  // loads is then no wait for copies).
   if constexpr (FOLD || LNRES) {
-    if (!ex.rows_in) {
+    if (!ex.rows_in && threadIdx.x < BM) {
       int tm, tn;
       tile_coords<ORDER>(t, n_tiles, tiles_n, &tm, &tn);
-      const int m = min(tm * BM + wm0 + lane, M - 1);
-      srow[0][wm0 + lane] = ln_row_factors<RING_MAX_PARTS>(
+      const int m = min(tm * BM + (int)threadIdx.x, M - 1);
+      srow[0][threadIdx.x] = ln_row_factors<RING_MAX_PARTS>(
           [&](int q) { return ex.stats_in[(size_t)q * M + m]; }, ex.parts_in, ex.eps);
     }
   }
@@ -150,11 +162,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
   for (int s = 0; s < 2; ++s) {
     const uint32_t go = more();
 #pragma unroll
-    for (int c = 0; c < 8; ++c) copy(c, s, go);
+    for (int c = 0; c < CPS; ++c) copy(c, s, go);
     if (s == 0 || go) advance();
   }
   if (more())
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPS) : "memory");
   else
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -192,12 +204,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 #pragma unroll
       for (int j = 0; j < TJ; ++j) acc[i][j] = Acc{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // The tile's first stage: its W and j = 0 rows landed before the last
+    // The tile's first stage: its W and phase-0 rows landed before the last
     // barrier A.
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      read_x0(0, ks);
-      read_x0(1, ks);
+#pragma unroll
+      for (int j = 0; j < J0; ++j) read_x0(j, ks);
 #pragma unroll
       for (int i = 0; i < TI; ++i) read_w(i, ks);
     }
@@ -205,20 +217,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     for (int kt = 0; kt < nkt; ++kt) {
       const bool last = kt == nkt - 1;
       const uint32_t go = more();
-      // Phase j = 0: 16 steps of two MFMAs.
+      // Phase 0: 16 steps of two MFMAs.
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const int ks = q >> 3, i = q & 7;
-        acc[i][0] = mma(fw[i][ks], f0[0][ks], acc[i][0]);
-        acc[i][1] = mma(fw[i][ks], f0[1][ks], acc[i][1]);
+        const int ks = q >> 3, i = (q & 7) * 2 / J0, j = (q & 7) * 2 % J0;
+        acc[i][j] = mma(fw[i][ks], f0[j][ks], acc[i][j]);
+        acc[i][j + 1] = mma(fw[i][ks], f0[j + 1][ks], acc[i][j + 1]);
         if (q == 3) {
-          // Barrier B: the j = 1 rows of this stage have landed (at a tile's
-          // first stage they had before the previous epilogue's first
-          // store); W and the j = 0 rows are read out.  8 copies, or more,
-          // were issued after those waited for, unless the stream has ended.
+          // Barrier B: the phase-1 rows of this stage have landed (at a
+          // tile's first stage they had before the previous epilogue's first
+          // store); W and the phase-0 rows are read out.  CPS copies, or
+          // more, were issued after those waited for, unless the stream has
+          // ended.
           if (kt > 0) {
             if (go)
-              asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+              asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPS) : "memory");
             else
               asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           }
@@ -229,12 +242,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
         if (q >= 5 && (q & 1)) copy((q - 5) >> 1, p, go);
         __builtin_amdgcn_sched_barrier(0);
       }
-      // Barrier A: W and the j = 0 rows of the next stage have landed (at a
-      // tile's first stage as above); the j = 1 rows are read out.  (A tile
+      // Barrier A: W and the phase-0 rows of the next stage have landed (at a
+      // tile's first stage as above); the phase-1 rows are read out.  (A tile
       // of one stage publishes its per-feature vectors here.)
       if (kt > 0 || first || nkt == 1) {
         if (go && nkt > 1)
-          asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPS) : "memory");
         else
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
@@ -246,18 +259,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
       for (int ks = 0; ks < 2; ++ks) {
         aw[ks] += other;
         ax[ks] += other;
+        ax1[ks] += other;
       }
       const uint32_t go1 = lane_mask(go && !last);
       __builtin_amdgcn_sched_barrier(0);
-      // Phase j = 1 (the fragments read at a tile's last stage are not used).
+      // Phase 1 (the fragments read at a tile's last stage are not used):
+      // 2 TI steps of two MFMAs; the 2 J0 phase-0 fragments of the next stage
+      // over the last steps.
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int ks = q >> 3, i = q & 7;
-        acc[i][2] = mma(fw[i][ks], f1[0][ks], acc[i][2]);
-        acc[i][3] = mma(fw[i][ks], f1[1][ks], acc[i][3]);
+      for (int q = 0; q < 2 * TI; ++q) {
+        const int ks = q / TI, i = q % TI;
+        acc[i][J0] = mma(fw[i][ks], f1[0][ks], acc[i][J0]);
+        acc[i][J0 + 1] = mma(fw[i][ks], f1[1][ks], acc[i][J0 + 1]);
         read_w(i, ks);
-        if (i >= 6) read_x0(i - 6, ks);
-        if (q == 1 || q == 3) copy(6 + (q >> 1), p, go1);
+        if (i >= TI - J0) read_x0(i - (TI - J0), ks);
+        if ((q & 1) && q / 2 < C1) copy(6 + q / 2, p, go1);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (go1) advance();
@@ -265,12 +281,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     }
     first = false;
 
-    // Region rows 0 .. 15 beside the stages, rows 16 .. 31 in this wave's
-    // copy slots of the j = 1 rows of the last stage's parity.
-    u32x4* const spare = smem + SPARE / 16 + wave * 128;
-    u32x4* const slots = smem + (X0 + (p ^ 1) * BUF + HALF) / 16 + wave * 64;
+    // The first region rows beside the stages, the last 8 C1 in this wave's
+    // copy slots of the phase-1 rows of the last stage's parity.
+    u32x4* const spare = smem + SPARE / 16 + wave * (SPARE_ROWS * 8);
+    u32x4* const slots = smem + ((p ^ 1) * BUF + X1) / 16 + wave * 64;
     auto slot16 = [&](int r, int c) -> u32x4* {
-      return r < 16 ? spare + r * 8 + c : slots + (r < 24 ? 0 : 512) + (r & 7) * 8 + c;
+      if (r < SPARE_ROWS) return spare + r * 8 + c;
+      return slots + (r - SPARE_ROWS >= 8 ? 512 : 0) + (r & 7) * 8 + c;
     };
     auto vec = [&](int v, int q) { return svec[tpar][v][(wn0 >> 2) + q]; };
     auto rows = [&](int r) {
@@ -281,8 +298,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 
     // The held-back copies, into slots only this wave has used since.
     const uint32_t go = more();
-    copy(6, p ^ 1, go);
-    copy(7, p ^ 1, go);
+#pragma unroll
+    for (int c = 6; c < CPS; ++c) copy(c, p ^ 1, go);
     if (go) advance();
     tpar ^= 1;
     t += G;
@@ -290,21 +307,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
   }
 }
 
-}  // namespace
-
-hipError_t launch_linear_wide(const uint16_t* X, const uint16_t* W, const float* bias,
-                              const uint16_t* R, uint16_t* Y, int64_t M, int N, int K, int epi,
-                              const LinearExtra& ex, hipStream_t stream) {
+template <int BM, int WAVES_M, int WAVES_N, int TI, int J0>
+hipError_t launch_wide_tiles(const uint16_t* X, const uint16_t* W, const float* bias,
+                             const uint16_t* R, uint16_t* Y, int64_t M, int N, int K, int epi,
+                             const LinearExtra& ex, hipStream_t stream) {
+  const int tiles_n = N / 256;
+  const int64_t n_tiles = (M + BM - 1) / BM * tiles_n;
   const bool factors = epi == EPI_FOLD || epi == EPI_FOLD_GELU || epi == EPI_LNRES_STATS;
-  if (factors && !ex.rows_in && (ex.parts_in > RING_MAX_PARTS || (M + 255) / 256 * (N / 256) > ex.n_cus))
+  if (factors && !ex.rows_in && (ex.parts_in > RING_MAX_PARTS || n_tiles > ex.n_cus))
     return hipErrorInvalidValue;
   if (2 * K >= 1 << 24) return hipErrorInvalidValue;  // copy offsets: 24-bit row strides
-  const int tiles_n = N / 256;
-  const int n_tiles = (int)((M + 255) / 256 * tiles_n);
-  const dim3 grid((unsigned)std::min(n_tiles, ex.n_cus)), block(512);
-#define SURGE_LAUNCH_EPI(E, O)                                                               \
-  hipLaunchKernelGGL((linear_wide_kernel<E, O>), grid, block, 0, stream, X, W, bias, R, Y, (int)M, \
-                     N, K, tiles_n, n_tiles, ex)
+  const dim3 grid((unsigned)std::min<int64_t>(n_tiles, ex.n_cus)), block(512);
+#define SURGE_LAUNCH_EPI(E, O)                                                                 \
+  hipLaunchKernelGGL((linear_wide_kernel<WAVES_M, WAVES_N, TI, J0, 2, E, O>), grid, block, 0, \
+                     stream, X, W, bias, R, Y, (int)M, N, K, tiles_n, (int)n_tiles, ex)
   switch (epi) {
     case EPI_BIAS: SURGE_LAUNCH_EPI(EPI_BIAS, ORDER_ROW_GROUPS); break;
     case EPI_BIAS_GELU: SURGE_LAUNCH_EPI(EPI_BIAS_GELU, ORDER_FEATURE_HALVES); break;
@@ -316,6 +332,15 @@ hipError_t launch_linear_wide(const uint16_t* X, const uint16_t* W, const float*
   }
 #undef SURGE_LAUNCH_EPI
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_linear_wide(int rows, const uint16_t* X, const uint16_t* W, const float* bias,
+                              const uint16_t* R, uint16_t* Y, int64_t M, int N, int K, int epi,
+                              const LinearExtra& ex, hipStream_t stream) {
+  if (rows == 192) return launch_wide_tiles<192, 2, 4, 4, 4>(X, W, bias, R, Y, M, N, K, epi, ex, stream);
+  return launch_wide_tiles<256, 4, 2, 8, 2>(X, W, bias, R, Y, M, N, K, epi, ex, stream);
 }
 
 }  // namespace surge

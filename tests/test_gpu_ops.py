@@ -449,3 +449,35 @@ def test_tile_families_match_bit_for_bit(N, epi):
         assert torch.equal(ys, y[a:a + n]), a
         if epi >= 5:
             assert torch.equal(ss, st[:, a:a + n]), a
+
+
+@pytest.mark.parametrize("epi", range(7))
+@pytest.mark.parametrize("N,M", [(256, 192 * 200 + 5), (512, 192 * 127 + 191)])
+def test_192_row_tiles_match_bit_for_bit(N, M, epi):
+    """Row counts that fill one round of 192 x 256 tiles (even and odd numbers
+    of K stages, ragged last tile) against calls of 3,000 rows."""
+    torch = torch_cuda()
+    g = torch.Generator(device="cuda").manual_seed(N + epi)
+    for K in (512, 576):
+        def randn(*dims):
+            return torch.randn(dims, generator=g, device="cuda")
+
+        x, w, b = randn(M, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
+        res = randn(M, N).bfloat16() if epi in (2, 5, 6) else None
+        raw = (res if epi == 6 else x).float().view(M, -1, 64)
+        st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)
+        vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N)) if epi >= 3 else (None,) * 3
+
+        def call(a, e):
+            y = torch.empty((e - a, N), dtype=torch.bfloat16, device="cuda")
+            st = torch.zeros((N // 64, e - a, 2), device="cuda")
+            S.surge_op_linear_ln(e - a, N, K, x[a:e], w, b, None if res is None else res[a:e], epi,
+                                 st_in[a:e].transpose(0, 1).contiguous(), st_in.shape[1], *vecs,
+                                 1e-12, st, y)
+            return y, st
+
+        y, st = call(0, M)
+        for a in (0, M // 2 // 8 * 8, (M - 3000) // 8 * 8):
+            ys, ss = call(a, a + 3000)
+            assert torch.equal(ys, y[a:a + 3000]), (K, a)
+            assert epi < 5 or torch.equal(ss, st[:, a:a + 3000]), (K, a)
