@@ -404,6 +404,8 @@ struct Choice {
 };
 static Choice linear_family(int64_t M, int N, int K, int n_cus) {
   if (ring_tile(M, N, n_cus) != RING_NONE) return {FAMILY_RING, 0};
+  // The wide tiles' copy offsets are products of 24-bit numbers.
+  if (K >= 1 << 23) return {FAMILY_MID, 0};
   if (N % 256 == 0) {
     const int rows = tile_rows(M, N, K, n_cus);
     return {rows == 128 ? FAMILY_MID : FAMILY_WIDE, rows};

@@ -197,8 +197,25 @@ surge_status check_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* d_
   return SURGE_OK;
 }
 
+// Whether the linear layer merges its input's statistics partials itself, so
+// that no row factors are needed.  Not where one of its outputs overlaps the
+// partials (statistics updated in place): a tile would write what another
+// still has to read, and the row-factor kernel reads them all first.
+bool merges_stats(int64_t M, int32_t N, int32_t K, const float* d_stats_in, int32_t parts_in,
+                  const float* d_stats_out, const uint16_t* d_y, int n_cus) {
+  const uintptr_t in = (uintptr_t)d_stats_in;
+  const uint64_t bytes = (uint64_t)M * (uint64_t)parts_in * 8u;
+  auto overlaps = [&](const void* p, uint64_t n) {
+    return p && (uintptr_t)p < in + bytes && in < (uintptr_t)p + n;
+  };
+  if (overlaps(d_stats_out, (uint64_t)M * (uint64_t)(N / linear_stats_width(M, N)) * 8u) ||
+      overlaps(d_y, (uint64_t)M * (uint64_t)N * 2u))
+    return false;
+  return linear_merges_stats(M, N, K, parts_in, n_cus);
+}
+
 // Enqueue the row factors (when `rows` is not NULL) and the linear layer,
-// which merges the partials itself otherwise (linear_merges_stats).
+// which merges the partials itself otherwise (merges_stats).
 surge_status enqueue_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t* d_x,
                                const uint16_t* d_w, const float* d_bias, const uint16_t* d_res,
                                int32_t epilogue, const float* d_stats_in, int32_t parts_in,
@@ -241,7 +258,8 @@ surge_status surge_op_linear_ln(int64_t M, int32_t N, int32_t K, const uint16_t*
   int n_cus = 0;
   HIP_TRY(resolve_cus(&n_cus));
   DeviceBuf rows;  // per-row LayerNorm factors, freed on return
-  if (factors && !linear_merges_stats(M, N, K, parts_in, n_cus)) HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
+  if (factors && !merges_stats(M, N, K, d_stats_in, parts_in, d_stats_out, d_y, n_cus))
+    HIP_TRY(hipMalloc(&rows.ptr, (size_t)M * 8));
   st = enqueue_linear_ln(M, N, K, d_x, d_w, d_bias, d_res, epilogue, d_stats_in, parts_in, d_col_s,
                          d_gamma, d_beta, eps, d_stats_out, d_y, (float2*)rows.ptr, n_cus, s);
   if (st != SURGE_OK) return st;
@@ -268,7 +286,7 @@ surge_status surge_op_linear_ln_noalloc(int64_t M, int32_t N, int32_t K, const u
                 (long long)M, (long long)kScratchRows);
   int n_cus = 0;
   HIP_TRY(resolve_cus(&n_cus));
-  if (factors && !linear_merges_stats(M, N, K, parts_in, n_cus)) {
+  if (factors && !merges_stats(M, N, K, d_stats_in, parts_in, d_stats_out, d_y, n_cus)) {
     st = scratch_address(&rows);
     if (st != SURGE_OK) return st;
   }

@@ -481,3 +481,31 @@ def test_192_row_tiles_match_bit_for_bit(N, M, epi):
             ys, ss = call(a, a + 3000)
             assert torch.equal(ys, y[a:a + 3000]), (K, a)
             assert epi < 5 or torch.equal(ss, st[:, a:a + 3000]), (K, a)
+
+
+@pytest.mark.parametrize("M", [24, 2080, 5003, 13_579])
+def test_statistics_updated_in_place(M):
+    """Residual statistics read from and written to one buffer, in the sizes
+    of every tile family: the same as with two buffers."""
+    torch = torch_cuda()
+    N, K = 768, 128
+    g = torch.Generator(device="cuda").manual_seed(M)
+
+    def randn(*dims):
+        return torch.randn(dims, generator=g, device="cuda")
+
+    x, w, b = randn(M, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
+    res = randn(M, N).bfloat16()
+    raw = res.float().view(M, -1, 64)
+    st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2).transpose(0, 1).contiguous()
+    gamma, beta = 1 + 0.1 * randn(N), 0.1 * randn(N)
+    for op in (S.surge_op_linear_ln, S.surge_op_linear_ln_noalloc):
+        got = []
+        for in_place in (False, True):
+            a = st_in.clone()
+            out = a if in_place else torch.zeros_like(a)
+            y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+            op(M, N, K, x, w, b, res, 6, a, N // 64, None, gamma, beta, 1e-12, out, y)
+            got.append((y, out))
+        assert torch.equal(got[0][0], got[1][0])
+        assert torch.equal(got[0][1], got[1][1])
