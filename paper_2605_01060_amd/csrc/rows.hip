@@ -7,6 +7,8 @@
 // the variance is taken about the mean).
 #include <math.h>
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -59,72 +61,144 @@ __device__ __forceinline__ void ln_row(float (&v)[MAXC][8], int nch, int lane, i
   }
 }
 
+// Sum over the LPR (16 or 32) lanes of a row: four rotations inside 16 lanes
+// on the VALU, then the other half.  Every lane ends with the same bits.
+template <int LPR>
+__device__ __forceinline__ float group_sum(float v) {
+  auto rotated = [](float x, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  v += rotated(v, std::integral_constant<int, 0x128>());  // row_ror:8
+  v += rotated(v, std::integral_constant<int, 0x124>());
+  v += rotated(v, std::integral_constant<int, 0x122>());
+  v += rotated(v, std::integral_constant<int, 0x121>());
+  if constexpr (LPR == 32) v += __shfl_xor(v, 16, 64);
+  return v;
+}
+
 // One workgroup per `rows` rows of a work item (a 32-row block of a text),
-// so a long text is spread over several workgroups; the four waves take its
-// rows in turn.  A wave loads all its token IDs at once (one per lane) and
-// fetches a row's table chunks two rows ahead of the LayerNorm, so the
-// gathers of three rows are in flight.
+// so a long text is spread over several workgroups.  LPR lanes take a row,
+// C 16-byte chunks each, so a wave works on R = 64 / LPR rows at once and
+// keeps its chunks of gamma and beta (8 bytes per feature, twice what the
+// tables hold) in registers instead of loading them for every row; a row's
+// two reductions are VALU rotations.  A wave loads all its token IDs at once
+// (one per lane) and fetches the tables' chunks of its next R rows before it
+// normalises the current ones.
+//
+// Bound by HBM (a byte out per byte gathered); before, one wave took a row:
+// a third of its lanes idle at d = 768, gamma and beta loaded per row, and
+// twelve LDS shuffles in two chains.  2000 texts of ~54 tokens, us per call
+// (20 to 50 of them the host's), one row per wave / this / with STREAM_OUT: d = 768 139.7 / 109.7 / 86.9, 384 97 / 69 / 68, 1024 131 / 117 /
+// 112, 128 92 / 50 / 48.
+template <int LPR, int C, bool STREAM_OUT>
 __global__ __launch_bounds__(256) void embed_ln_kernel(
     const int32_t* __restrict__ tokens, const RowBlock* __restrict__ items, int rows,
     const uint16_t* __restrict__ word, const uint16_t* __restrict__ pos,
     const float* __restrict__ gamma, const float* __restrict__ beta, float eps, int vocab, int d,
     uint16_t* __restrict__ out, int* __restrict__ err) {
+  constexpr int R = 64 / LPR;
   const RowBlock item = items[blockIdx.x];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
+  const int g = lane / LPR;  // this lane's row of the R
+  const int gl = lane % LPR;
   const int beg = (int)item.beg;
-  const int r0 = (int)(item.len_block & 127u) * 32 + (int)blockIdx.y * rows + wave;
-  const int r1 = min((int)(item.len_block & 127u) * 32 + ((int)blockIdx.y + 1) * rows,
-                     (int)(item.len_block >> 7));
-  if (r0 >= r1) return;
-  const int n = (r1 - r0 + 3) >> 2;  // this wave's rows: r0, r0 + 4, ...
+  const int first = (int)(item.len_block & 127u) * 32 + (int)blockIdx.y * rows + wave * R;
+  const int end = min((int)(item.len_block & 127u) * 32 + ((int)blockIdx.y + 1) * rows,
+                      (int)(item.len_block >> 7));
+  if (first >= end) return;
+  // The wave's rows: first + 4 R i + r, r < R, its trip i.
+  const int trips = (end - first + 4 * R - 1) / (4 * R);
   const int nch = d >> 3;
   int ids = 0;
-  if (lane < n) {
-    ids = tokens[beg + r0 + 4 * lane];
-    if (ids < 0 || ids >= vocab) {
-      atomicOr(err, 1);
-      ids = 0;
+  {
+    const int p = first + lane / R * (4 * R) + lane % R;  // trip lane / R, row lane % R
+    if (lane < trips * R && p < end) {
+      ids = tokens[beg + p];
+      if (ids < 0 || ids >= vocab) {
+        atomicOr(err, 1);
+        ids = 0;
+      }
     }
   }
-  uint4 w[3][MAXC], q[3][MAXC];
-  // Table chunks of the wave's i-th row (word row of its checked ID,
-  // position row).
-  auto fetch = [&](int i, int slot) {
-    const int id = __builtin_amdgcn_readlane(ids, i);
-    const uint4* wr = reinterpret_cast<const uint4*>(word + (size_t)id * d);
-    const uint4* pr = reinterpret_cast<const uint4*>(pos + (size_t)(r0 + 4 * i) * d);
+  float ga[C][8], be[C][8];
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-      const int ch = lane + 64 * c;
-      if (ch < nch) {
-        w[slot][c] = wr[ch];
-        q[slot][c] = pr[ch];
-      }
+  for (int c = 0; c < C; ++c) {
+    const int ch = min(gl + LPR * c, nch - 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float4 a = reinterpret_cast<const float4*>(gamma)[2 * ch + h];
+      const float4 b = reinterpret_cast<const float4*>(beta)[2 * ch + h];
+      ga[c][4 * h] = a.x, ga[c][4 * h + 1] = a.y, ga[c][4 * h + 2] = a.z, ga[c][4 * h + 3] = a.w;
+      be[c][4 * h] = b.x, be[c][4 * h + 1] = b.y, be[c][4 * h + 2] = b.z, be[c][4 * h + 3] = b.w;
+    }
+  }
+  uint4 w[2][C], q[2][C];
+  // Table chunks of the wave's trip i (word rows of its checked IDs, position
+  // rows; a group without a row reads the last one's position and ID 0).
+  auto fetch = [&](int i, int slot) {
+    const int id = __shfl(ids, i * R + g, 64);
+    const int p = min(first + 4 * R * i + g, end - 1);
+    const uint4* wr = reinterpret_cast<const uint4*>(word + (size_t)id * d);
+    const uint4* pr = reinterpret_cast<const uint4*>(pos + (size_t)p * d);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int ch = min(gl + LPR * c, nch - 1);
+      w[slot][c] = wr[ch];
+      q[slot][c] = pr[ch];
     }
   };
+  const float inv_d = 1.0f / (float)d;
   auto row = [&](int i, int slot) {
-    float v[MAXC][8];
+    float v[C][8];
+    float s = 0.0f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-      if (lane + 64 * c < nch) {
-        float a[8], b[8];
-        unpack8(w[slot][c], a);
-        unpack8(q[slot][c], b);
+    for (int c = 0; c < C; ++c) {
+      float a[8], b[8];
+      unpack8(w[slot][c], a);
+      unpack8(q[slot][c], b);
+      const bool in = gl + LPR * c < nch;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[c][e] = a[e] + b[e];
+      for (int e = 0; e < 8; ++e) {
+        v[c][e] = a[e] + b[e];
+        s += in ? v[c][e] : 0.0f;
       }
     }
-    if (i + 3 < n) fetch(i + 3, slot);
-    ln_row(v, nch, lane, d, gamma, beta, eps, out + (size_t)(beg + r0 + 4 * i) * d);
+    if (i + 2 < trips) fetch(i + 2, slot);
+    const float mean = group_sum<LPR>(s) * inv_d;
+    float sq = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const bool in = gl + LPR * c < nch;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[c][e] -= mean;
+        sq = in ? fmaf(v[c][e], v[c][e], sq) : sq;
+      }
+    }
+    const float rstd = 1.0f / sqrtf(fmaf(group_sum<LPR>(sq), inv_d, eps));
+    const int p = first + 4 * R * i + g;
+    u32x4* y = reinterpret_cast<u32x4*>(out + (size_t)(beg + p) * d);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = fmaf(v[c][e] * rstd, ga[c][e], be[c][e]);
+      const u32x4 packed = __builtin_bit_cast(u32x4, pack8(o));
+      if (p < end && gl + LPR * c < nch) {
+        if constexpr (STREAM_OUT)
+          __builtin_nontemporal_store(packed, y + gl + LPR * c);
+        else
+          y[gl + LPR * c] = packed;
+      }
+    }
   };
   fetch(0, 0);
-  if (n > 1) fetch(1, 1);
-  if (n > 2) fetch(2, 2);
-  for (int i = 0; i < n; i += 3) {
+  if (trips > 1) fetch(1, 1);
+  for (int i = 0; i < trips; i += 2) {
     row(i, 0);
-    if (i + 1 < n) row(i + 1, 1);
-    if (i + 2 < n) row(i + 2, 2);
+    if (i + 1 < trips) row(i + 1, 1);
   }
 }
 
@@ -243,12 +317,35 @@ hipError_t launch_embed_ln(const int32_t* tokens, const RowBlock* items, int n_i
                            const float* beta, float eps, int vocab, int d, uint16_t* out, int* err,
                            int n_cus, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  // Whole 32-row items once they fill the chip (8 workgroups per CU);
-  // fewer rows per workgroup, down to one per wave, while they do not.
+  // 16 lanes a row up to d = 512 (4 rows per wave), then 32 (2 rows): at most
+  // four chunks per lane.
+  const int lpr = d <= 512 ? 16 : 32;
+  // Whole 32-row items once they fill the chip (8 workgroups per CU); fewer
+  // rows per workgroup, down to one trip of its waves, while they do not.
   int split = 1;
-  while (split < 8 && (int64_t)n_items * split * 2 <= (int64_t)n_cus * 8) split *= 2;
-  hipLaunchKernelGGL(embed_ln_kernel, dim3(n_items, split), dim3(256), 0, stream, tokens, items,
-                     32 / split, word, pos, gamma, beta, eps, vocab, d, out, err);
+  while (split < lpr / 8 && (int64_t)n_items * split * 2 <= (int64_t)n_cus * 8) split *= 2;
+  // An output that does not fit the L2s (8 x 4 MB) is stored nontemporally,
+  // which leaves them to the tables' rows; a smaller one stays for the layer
+  // that reads it next (57 MiniLM texts, 1.5 MB: 271 us per call, 274 with
+  // nontemporal stores).
+  const bool stream_out = (int64_t)n_items * 32 * d * 2 > (int64_t)32 << 20;
+#define SURGE_EMBED(L, C)                                                                      \
+  if (stream_out)                                                                              \
+    hipLaunchKernelGGL((embed_ln_kernel<L, C, true>), dim3(n_items, split), dim3(256), 0, stream, \
+                       tokens, items, 32 / split, word, pos, gamma, beta, eps, vocab, d, out, err); \
+  else                                                                                         \
+    hipLaunchKernelGGL((embed_ln_kernel<L, C, false>), dim3(n_items, split), dim3(256), 0, stream, \
+                       tokens, items, 32 / split, word, pos, gamma, beta, eps, vocab, d, out, err)
+  switch ((d / 8 + lpr - 1) / lpr * 100 + lpr) {
+    case 116: SURGE_EMBED(16, 1); break;
+    case 216: SURGE_EMBED(16, 2); break;
+    case 316: SURGE_EMBED(16, 3); break;
+    case 416: SURGE_EMBED(16, 4); break;
+    case 332: SURGE_EMBED(32, 3); break;
+    case 432: SURGE_EMBED(32, 4); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef SURGE_EMBED
   return hipGetLastError();
 }
 

@@ -509,3 +509,31 @@ def test_statistics_updated_in_place(M):
             got.append((y, out))
         assert torch.equal(got[0][0], got[1][0])
         assert torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("d", range(128, 1025, 128))
+def test_embed_ln_every_width(d):
+    """Every width's lane layout, in calls small enough to split a 32-row
+    block over workgroups and too large for it."""
+    torch = torch_cuda()
+    g = torch.Generator(device="cuda").manual_seed(d)
+    vocab, max_pos = 700, 70
+
+    def randn(*dims):
+        return torch.randn(dims, generator=g, device="cuda")
+
+    word, pos = (randn(vocab, d) * 0.02).bfloat16(), (randn(max_pos, d) * 0.02).bfloat16()
+    gamma, beta = 1 + 0.02 * randn(d), 0.02 * randn(d)
+    for times in (1, 300):
+        lengths = np.array([1, 2, 5, 15, 17, 31, 32, 33, 47, 64, 65, 70] * times)
+        cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+        tok = torch.randint(0, vocab, (int(cu[-1]),), generator=g, device="cuda", dtype=torch.int32)
+        out = torch.full((int(cu[-1]), d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        S.surge_op_embed_ln(cu, tok, word, vocab, pos, max_pos, gamma, beta, 1e-12, d, out)
+        p = torch.from_numpy(np.concatenate([np.arange(n) for n in lengths])).cuda()
+        v = word[tok.long()].double() + pos[p].double()
+        mu = v.mean(1, keepdim=True)
+        ref = (v - mu) / torch.sqrt(((v - mu) ** 2).mean(1, keepdim=True) + 1e-12) \
+            * gamma.double() + beta.double()
+        err = (out.double() - ref).abs() - BF16_REL * ref.abs()
+        assert float(err.max()) <= 1e-4, (times, float(err.max()))
