@@ -33,18 +33,25 @@ from typing import Dict, List, Optional, Tuple
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 
-# kernel class -> source file of its kernel
-KERNEL_SOURCES = {"qkv": "linear.hip", "oproj": "linear.hip", "ffn1": "linear.hip",
-                  "ffn2": "linear.hip", "attn": "attention.hip", "layernorm": "rows.hip"}
+# kernel class -> source files of its kernels
+LINEAR_SOURCES = ("linear.hip", "linear_common.h", "linear_ring.hip", "linear_wide.hip")
+KERNEL_SOURCES = {"qkv": LINEAR_SOURCES, "oproj": LINEAR_SOURCES, "ffn1": LINEAR_SOURCES,
+                  "ffn2": LINEAR_SOURCES, "attn": ("attention.hip",), "layernorm": ("rows.hip",)}
 KERNEL_CLASSES = tuple(KERNEL_SOURCES)
 COPY_KERNEL = "copyBuffer"
 
 
 def _epi(name: str) -> int:
-    """Epilogue of a linear kernel instance: the template argument before
-    the tile order (the last one)."""
-    m = re.search(r"linear_bf16_kernel<([^>]*)>", name)
-    return int(m.group(1).split(",")[-2]) if m else -1
+    """Epilogue of a linear kernel instance: the last template argument of
+    the small-chunk tiles, otherwise the one before the tile order (which the
+    128-wide tiles follow by whether they merge row statistics)."""
+    m = re.search(r"linear_(bf16|ring|wide)_kernel<([^>]*)>", name)
+    if not m:
+        return -1
+    args = [a.strip() for a in m.group(2).split(",")]
+    if args[-1] in ("true", "false"):
+        args.pop()
+    return int(args[-1 if m.group(1) == "ring" else -2])
 
 
 def name_class(name: str) -> Optional[str]:
@@ -53,7 +60,7 @@ def name_class(name: str) -> Optional[str]:
     row statistics, 6 residual LN + row statistics).  The O-projection and
     FFN2 run the same residual-epilogue instance and come back as
     "residual"; `dispatch_classes` tells them apart."""
-    if "linear_bf16_kernel" in name:
+    if _epi(name) >= 0:
         return {0: "qkv", 3: "qkv", 1: "ffn1", 4: "ffn1",
                 2: "residual", 5: "residual", 6: "residual"}.get(_epi(name))
     if "attention_varlen_kernel" in name:
@@ -98,9 +105,8 @@ def _dispatches(path: str) -> List[Dict]:
 
 
 def source_hash(kernel_class: str) -> str:
-    fname = KERNEL_SOURCES[kernel_class]
     h = hashlib.sha256()
-    for f in (fname, "device_common.h"):
+    for f in KERNEL_SOURCES[kernel_class] + ("device_common.h",):
         with open(os.path.join(PKG, "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

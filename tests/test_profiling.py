@@ -200,3 +200,14 @@ def test_fabric_reads_count_each_request_at_its_size(tmp_path):
     assert res["ffn1"]["dispatches"] == 2
     assert res["ffn1"]["read_bytes_per_launch"] == pytest.approx(2000.0 * 128 + 640 + 64)
     assert res["ffn1"]["accounted"] == pytest.approx(1.0)
+
+
+@pytest.mark.parametrize("kernel", ["linear_bf16_kernel<{epi}, {order}, true>",
+                                    "linear_bf16_kernel<{epi}, {order}, false>",
+                                    "linear_wide_kernel<4, 2, 8, 2, 2, {epi}, {order}>",
+                                    "linear_ring_kernel<32, 64, 1, 2, 3, {epi}>"])
+def test_every_tile_family_is_classified(kernel):
+    name = "void surge::(anonymous namespace)::" + kernel + "(x)"
+    for epi, cls in enumerate(["qkv", "ffn1", "residual", "qkv", "ffn1", "residual", "residual"]):
+        assert P._epi(name.format(epi=epi, order=1)) == epi
+        assert P.name_class(name.format(epi=epi, order=1)) == cls
