@@ -1,12 +1,13 @@
 // Row-wise, HBM-bound kernels: embedding gather + LayerNorm, LayerNorm, and
 // masked mean pooling + L2 normalisation + partition scatter.
 //
-// A row of d bf16 values is read as d/8 16-byte chunks spread over the 64
-// lanes of one wave (at most two chunks per lane for d <= 1024); mean and
-// variance are wave reductions in fp32 (two passes over the registers, so
-// the variance is taken about the mean).
+// A row of d bf16 values is read as d/8 16-byte chunks spread over 16 or 32
+// lanes of a wave (at most four chunks per lane for d <= 1024); mean and
+// variance are reductions over them in fp32 (two passes over the registers,
+// so the variance is taken about the mean).
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -14,52 +15,6 @@
 
 namespace surge {
 namespace {
-
-constexpr int MAXC = 2;  // 16-byte chunks per lane, d <= 64 * 2 * 8 = 1024
-
-__device__ __forceinline__ void ln_row(float (&v)[MAXC][8], int nch, int lane, int d,
-                                       const float* __restrict__ gamma,
-                                       const float* __restrict__ beta, float eps,
-                                       uint16_t* __restrict__ yrow) {
-  float s = 0.0f;
-#pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    if (lane + 64 * c < nch) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += v[c][e];
-    }
-  }
-  const float mean = wave_sum(s) / (float)d;
-  float q = 0.0f;
-#pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    if (lane + 64 * c < nch) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float t = v[c][e] - mean;
-        q += t * t;
-      }
-    }
-  }
-  const float var = wave_sum(q) / (float)d;
-  const float rstd = 1.0f / sqrtf(var + eps);
-#pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    const int ch = lane + 64 * c;
-    if (ch < nch) {
-      const float4 g0 = reinterpret_cast<const float4*>(gamma)[2 * ch];
-      const float4 g1 = reinterpret_cast<const float4*>(gamma)[2 * ch + 1];
-      const float4 b0 = reinterpret_cast<const float4*>(beta)[2 * ch];
-      const float4 b1 = reinterpret_cast<const float4*>(beta)[2 * ch + 1];
-      const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-      const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-      float o[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (v[c][e] - mean) * rstd * g[e] + b[e];
-      reinterpret_cast<uint4*>(yrow)[ch] = pack8(o);
-    }
-  }
-}
 
 // Sum over the LPR (16 or 32) lanes of a row: four rotations inside 16 lanes
 // on the VALU, then the other half.  Every lane ends with the same bits.
@@ -75,6 +30,61 @@ __device__ __forceinline__ float group_sum(float v) {
   v += rotated(v, std::integral_constant<int, 0x121>());
   if constexpr (LPR == 32) v += __shfl_xor(v, 16, 64);
   return v;
+}
+
+// A lane's chunks gl, gl + LPR, ... of a row's per-feature vector.
+template <int LPR, int C>
+__device__ __forceinline__ void load_vector(const float* __restrict__ src, int gl, int nch,
+                                            float (&v)[C][8]) {
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int ch = min(gl + LPR * c, nch - 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float4 a = reinterpret_cast<const float4*>(src)[2 * ch + h];
+      v[c][4 * h] = a.x, v[c][4 * h + 1] = a.y, v[c][4 * h + 2] = a.z, v[c][4 * h + 3] = a.w;
+    }
+  }
+}
+
+// LayerNorm of a row held by LPR lanes (v: in, then overwritten), stored to
+// y, nontemporally with STREAM_OUT, where `valid`.
+template <int LPR, int C, bool STREAM_OUT>
+__device__ __forceinline__ void ln_store(float (&v)[C][8], const float (&ga)[C][8],
+                                         const float (&be)[C][8], int gl, int nch, float inv_d,
+                                         float eps, bool valid, uint16_t* __restrict__ yrow) {
+  float s = 0.0f, sq = 0.0f;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const bool in = gl + LPR * c < nch;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s += in ? v[c][e] : 0.0f;
+  }
+  const float mean = group_sum<LPR>(s) * inv_d;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const bool in = gl + LPR * c < nch;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[c][e] -= mean;
+      sq = in ? fmaf(v[c][e], v[c][e], sq) : sq;
+    }
+  }
+  const float rstd = 1.0f / sqrtf(fmaf(group_sum<LPR>(sq), inv_d, eps));
+  u32x4* y = reinterpret_cast<u32x4*>(yrow);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = fmaf(v[c][e] * rstd, ga[c][e], be[c][e]);
+    const u32x4 packed = __builtin_bit_cast(u32x4, pack8(o));
+    if (valid && gl + LPR * c < nch) {
+      if constexpr (STREAM_OUT)
+        __builtin_nontemporal_store(packed, y + gl + LPR * c);
+      else
+        y[gl + LPR * c] = packed;
+    }
+  }
 }
 
 // One workgroup per `rows` rows of a work item (a 32-row block of a text),
@@ -123,17 +133,8 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(
     }
   }
   float ga[C][8], be[C][8];
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const int ch = min(gl + LPR * c, nch - 1);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const float4 a = reinterpret_cast<const float4*>(gamma)[2 * ch + h];
-      const float4 b = reinterpret_cast<const float4*>(beta)[2 * ch + h];
-      ga[c][4 * h] = a.x, ga[c][4 * h + 1] = a.y, ga[c][4 * h + 2] = a.z, ga[c][4 * h + 3] = a.w;
-      be[c][4 * h] = b.x, be[c][4 * h + 1] = b.y, be[c][4 * h + 2] = b.z, be[c][4 * h + 3] = b.w;
-    }
-  }
+  load_vector<LPR>(gamma, gl, nch, ga);
+  load_vector<LPR>(beta, gl, nch, be);
   uint4 w[2][C], q[2][C];
   // Table chunks of the wave's trip i (word rows of its checked IDs, position
   // rows; a group without a row reads the last one's position and ID 0).
@@ -152,47 +153,18 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(
   const float inv_d = 1.0f / (float)d;
   auto row = [&](int i, int slot) {
     float v[C][8];
-    float s = 0.0f;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       float a[8], b[8];
       unpack8(w[slot][c], a);
       unpack8(q[slot][c], b);
-      const bool in = gl + LPR * c < nch;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        v[c][e] = a[e] + b[e];
-        s += in ? v[c][e] : 0.0f;
-      }
+      for (int e = 0; e < 8; ++e) v[c][e] = a[e] + b[e];
     }
     if (i + 2 < trips) fetch(i + 2, slot);
-    const float mean = group_sum<LPR>(s) * inv_d;
-    float sq = 0.0f;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const bool in = gl + LPR * c < nch;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        v[c][e] -= mean;
-        sq = in ? fmaf(v[c][e], v[c][e], sq) : sq;
-      }
-    }
-    const float rstd = 1.0f / sqrtf(fmaf(group_sum<LPR>(sq), inv_d, eps));
     const int p = first + 4 * R * i + g;
-    u32x4* y = reinterpret_cast<u32x4*>(out + (size_t)(beg + p) * d);
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      float o[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = fmaf(v[c][e] * rstd, ga[c][e], be[c][e]);
-      const u32x4 packed = __builtin_bit_cast(u32x4, pack8(o));
-      if (p < end && gl + LPR * c < nch) {
-        if constexpr (STREAM_OUT)
-          __builtin_nontemporal_store(packed, y + gl + LPR * c);
-        else
-          y[gl + LPR * c] = packed;
-      }
-    }
+    ln_store<LPR, C, STREAM_OUT>(v, ga, be, gl, nch, inv_d, eps, p < end,
+                                 out + (size_t)(beg + p) * d);
   };
   fetch(0, 0);
   if (trips > 1) fetch(1, 1);
@@ -209,24 +181,41 @@ __global__ __launch_bounds__(256) void upload_kernel(const uint4* __restrict__ s
   if (i < n16) dst[i] = src[i];
 }
 
-// One wave per row, four rows per block.
+// Rows as in the embedding: LPR lanes a row, a wave's trips of R rows each,
+// the next trip's chunks fetched before the current rows are normalised (a
+// wave reads and writes rows of its own only, so y may be x).  Bound by HBM.
+// Against one row per wave, us per call of 107,000 rows (about 12 of them the
+// host's): d = 768 89.7 -> 62.9, 384 48.6 -> 37.6, 1024 94.3 -> 77.6, 128
+// 44.2 -> 21.5; one row 14.5 -> 13.5.
+template <int LPR, int C, bool STREAM_OUT>
 __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t* __restrict__ x,
                                                         const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, float eps,
-                                                        uint16_t* __restrict__ y, int64_t M,
-                                                        int d) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                        uint16_t* __restrict__ y, int64_t M, int d,
+                                                        int trips) {
+  constexpr int R = 64 / LPR;
   const int lane = threadIdx.x & 63;
-  if (row >= M) return;
+  const int gl = lane % LPR;
   const int nch = d >> 3;
-  const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * d);
-  float v[MAXC][8];
+  const float inv_d = 1.0f / (float)d;
+  int64_t row = ((int64_t)blockIdx.x * trips * 4 + (threadIdx.x >> 6)) * R + lane / LPR;
+  uint4 next[C];
+  auto fetch = [&](int64_t r) {
+    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)min(r, M - 1) * d);
 #pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    const int ch = lane + 64 * c;
-    if (ch < nch) unpack8(xr[ch], v[c]);
+    for (int c = 0; c < C; ++c) next[c] = xr[min(gl + LPR * c, nch - 1)];
+  };
+  fetch(row);
+  float ga[C][8], be[C][8];
+  load_vector<LPR>(gamma, gl, nch, ga);
+  load_vector<LPR>(beta, gl, nch, be);
+  for (int i = 0; i < trips; ++i, row += 4 * R) {
+    float v[C][8];
+#pragma unroll
+    for (int c = 0; c < C; ++c) unpack8(next[c], v[c]);
+    if (i + 1 < trips) fetch(row + 4 * R);
+    ln_store<LPR, C, STREAM_OUT>(v, ga, be, gl, nch, inv_d, eps, row < M, y + (size_t)row * d);
   }
-  ln_row(v, nch, lane, d, gamma, beta, eps, y + (size_t)row * d);
 }
 
 // One block per text: 2 groups of 128 threads split the text's rows, each
@@ -312,23 +301,39 @@ __global__ __launch_bounds__(256) void ln_rows_kernel(const float2* __restrict__
 
 }  // namespace
 
+// 16 lanes a row up to d = 512 (4 rows per wave), then 32 (2 rows): at most
+// four chunks per lane.
+static int lanes_per_row(int d) { return d <= 512 ? 16 : 32; }
+#define SURGE_ROW_LAYOUTS(d, LAUNCH)                                         \
+  switch (((d) / 8 + lanes_per_row(d) - 1) / lanes_per_row(d)) {             \
+    case 1: LAUNCH(16, 1); break;                                            \
+    case 2: LAUNCH(16, 2); break;                                            \
+    case 3:                                                                  \
+      if (d <= 512) { LAUNCH(16, 3); } else { LAUNCH(32, 3); }               \
+      break;                                                                 \
+    case 4:                                                                  \
+      if (d <= 512) { LAUNCH(16, 4); } else { LAUNCH(32, 4); }               \
+      break;                                                                 \
+    default: return hipErrorInvalidValue;                                    \
+  }
+
+// An output that does not fit the L2s (8 x 4 MB) is stored nontemporally,
+// which leaves them to the rows being read; a smaller one stays for the layer
+// that reads it next (57 MiniLM texts, 1.5 MB: 271 us per call, 274 with
+// nontemporal stores).
+constexpr int64_t STREAM_OUT_BYTES = (int64_t)32 << 20;
+
 hipError_t launch_embed_ln(const int32_t* tokens, const RowBlock* items, int n_items,
                            const uint16_t* word, const uint16_t* pos, const float* gamma,
                            const float* beta, float eps, int vocab, int d, uint16_t* out, int* err,
                            int n_cus, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  // 16 lanes a row up to d = 512 (4 rows per wave), then 32 (2 rows): at most
-  // four chunks per lane.
-  const int lpr = d <= 512 ? 16 : 32;
+  const int lpr = lanes_per_row(d);
   // Whole 32-row items once they fill the chip (8 workgroups per CU); fewer
   // rows per workgroup, down to one trip of its waves, while they do not.
   int split = 1;
   while (split < lpr / 8 && (int64_t)n_items * split * 2 <= (int64_t)n_cus * 8) split *= 2;
-  // An output that does not fit the L2s (8 x 4 MB) is stored nontemporally,
-  // which leaves them to the tables' rows; a smaller one stays for the layer
-  // that reads it next (57 MiniLM texts, 1.5 MB: 271 us per call, 274 with
-  // nontemporal stores).
-  const bool stream_out = (int64_t)n_items * 32 * d * 2 > (int64_t)32 << 20;
+  const bool stream_out = (int64_t)n_items * 32 * d * 2 > STREAM_OUT_BYTES;
 #define SURGE_EMBED(L, C)                                                                      \
   if (stream_out)                                                                              \
     hipLaunchKernelGGL((embed_ln_kernel<L, C, true>), dim3(n_items, split), dim3(256), 0, stream, \
@@ -336,15 +341,7 @@ hipError_t launch_embed_ln(const int32_t* tokens, const RowBlock* items, int n_i
   else                                                                                         \
     hipLaunchKernelGGL((embed_ln_kernel<L, C, false>), dim3(n_items, split), dim3(256), 0, stream, \
                        tokens, items, 32 / split, word, pos, gamma, beta, eps, vocab, d, out, err)
-  switch ((d / 8 + lpr - 1) / lpr * 100 + lpr) {
-    case 116: SURGE_EMBED(16, 1); break;
-    case 216: SURGE_EMBED(16, 2); break;
-    case 316: SURGE_EMBED(16, 3); break;
-    case 416: SURGE_EMBED(16, 4); break;
-    case 332: SURGE_EMBED(32, 3); break;
-    case 432: SURGE_EMBED(32, 4); break;
-    default: return hipErrorInvalidValue;
-  }
+  SURGE_ROW_LAYOUTS(d, SURGE_EMBED)
 #undef SURGE_EMBED
   return hipGetLastError();
 }
@@ -371,9 +368,21 @@ hipError_t launch_ln_rows(const float2* stats, int parts, int64_t M, float eps, 
 hipError_t launch_layernorm(const uint16_t* x, const float* gamma, const float* beta, float eps,
                             uint16_t* y, int64_t M, int d, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((M + 3) / 4);
-  hipLaunchKernelGGL(layernorm_kernel, dim3(blocks), dim3(256), 0, stream, x, gamma, beta, eps, y,
-                     M, d);
+  const int lpr = lanes_per_row(d), rows = 4 * 64 / lpr;  // rows of a workgroup's trip
+  // One trip while workgroups are few; eight, for gamma and beta's sake, once
+  // 2,048 workgroups remain.
+  const int trips = (int)std::min<int64_t>(std::max<int64_t>(M / (rows * 2048), 1), 8);
+  const dim3 grid((unsigned)((M + rows * trips - 1) / (rows * trips)));
+  const bool stream_out = M * d * 2 > STREAM_OUT_BYTES;
+#define SURGE_LAYERNORM(L, C)                                                                   \
+  if (stream_out)                                                                               \
+    hipLaunchKernelGGL((layernorm_kernel<L, C, true>), grid, dim3(256), 0, stream, x, gamma, beta, \
+                       eps, y, M, d, trips);                                                    \
+  else                                                                                          \
+    hipLaunchKernelGGL((layernorm_kernel<L, C, false>), grid, dim3(256), 0, stream, x, gamma,   \
+                       beta, eps, y, M, d, trips)
+  SURGE_ROW_LAYOUTS(d, SURGE_LAYERNORM)
+#undef SURGE_LAYERNORM
   return hipGetLastError();
 }
 

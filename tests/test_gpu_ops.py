@@ -537,3 +537,24 @@ def test_embed_ln_every_width(d):
             * gamma.double() + beta.double()
         err = (out.double() - ref).abs() - BF16_REL * ref.abs()
         assert float(err.max()) <= 1e-4, (times, float(err.max()))
+
+
+@pytest.mark.parametrize("d", [8, 120, 136, 384, 520, 776, 1016, 1024])
+@pytest.mark.parametrize("M", [1, 33, 40_003])
+def test_layernorm_lane_layouts(d, M):
+    """Chunk counts that leave lanes idle in either lane layout, calls of one
+    trip per wave and of several, and y written over x."""
+    torch = torch_cuda()
+    g = torch.Generator(device="cuda").manual_seed(d + M)
+    x = torch.randn(M, d, generator=g, device="cuda").bfloat16()
+    gamma = 1 + 0.1 * torch.randn(d, generator=g, device="cuda")
+    beta = 0.1 * torch.randn(d, generator=g, device="cuda")
+    v = x.double()
+    mu = v.mean(1, keepdim=True)
+    ref = (v - mu) / torch.sqrt(((v - mu) ** 2).mean(1, keepdim=True) + 1e-5) * gamma.double() \
+        + beta.double()
+    y = torch.full_like(x, float("nan"))
+    S.surge_op_layernorm(M, d, x, gamma, beta, 1e-5, y)
+    assert float(((y.double() - ref).abs() - BF16_REL * ref.abs()).max()) <= 1e-4
+    S.surge_op_layernorm(M, d, x, gamma, beta, 1e-5, x)
+    assert torch.equal(x, y)
