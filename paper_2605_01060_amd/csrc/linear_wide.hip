@@ -30,6 +30,13 @@
 // Measured against the loop of one-stage tolerance on 32x32x16 MFMAs that it
 // replaces (M = 262,144, us): QKV 898 -> 828, FFN2 1,132 -> 1,061, FFN1
 // 1,390 -> 1,309, O-projection 375 -> 364.
+//
+// No instance may spill: a spilled address that a copy uses brings a wait for
+// every copy in flight into the K loop.  One register did so in FFN1, FFN2 and
+// the O-projection; without it (M = 262,144, us, on zeros / on normal data)
+// FFN1 1,083 -> 1,057 / 1,310 -> 1,309, FFN2 887 -> 842 / 1,079 -> 1,074,
+// O-projection 325 -> 318 / 377 -> 373: on normal data the power limit takes
+// most of it back.
 #include <algorithm>
 
 #include "linear_common.h"
@@ -64,7 +71,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
   constexpr bool FOLD = EPI == EPI_FOLD || EPI == EPI_FOLD_GELU;
   constexpr bool LNRES = EPI == EPI_LNRES_STATS;
   constexpr int NV = 1 + (FOLD ? 1 : 0) + (LNRES ? 2 : 0);
-  __shared__ u32x4 smem[SPARE / 16 + 8 * SPARE_ROWS * 8];
+  __shared__ __attribute__((aligned(128))) u32x4 smem[SPARE / 16 + 8 * SPARE_ROWS * 8];
   // Per-feature vectors (bias, then col_s or gamma and beta) by tile parity.
   __shared__ float4 svec[2][NV][BN / 4];
   __shared__ float2 srow[2][FOLD || LNRES ? 256 : 1];  // LayerNorm factors of the tile's rows
@@ -77,22 +84,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
   const int nkt = K / 64;
   const int G = gridDim.x;
 
-  // Fragment addresses of stage parity 0: row lane % 16, then the swizzled
-  // 16-byte chunk of the 32-wide K step ks; fragments are 16 rows apart.
+  // Fragment addresses: row lane % 16, then the swizzled 16-byte chunk of the
+  // 32-wide K step ks, which for ks = 1 differs in bit 6 of the address only
+  // (rows are 128 bytes, aligned); fragments are 16 rows apart.
   const uint32_t lds = lds_address(smem);
-  uint32_t aw[2], ax[2], ax1[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const uint32_t ch = (uint32_t)swz<8>(lane & 15, ks * 4 + (lane >> 4)) * 16u;
-    aw[ks] = lds + (uint32_t)wn0 * 128u + ch;
-    ax[ks] = lds + X0 + (uint32_t)(wave_m * R0) * 128u + ch;
-    ax1[ks] = lds + X1 + (uint32_t)(wave_m * R1) * 128u + ch;
-  }
+  uint32_t aw, ax, ax1;
   bf16x8 fw[TI][2], f0[J0][2], f1[J1][2];
-  auto read_w = [&](int i, int ks) { fw[i][ks] = lds_fragment(aw[ks] + i * 2048); };
-  auto read_x0 = [&](int j, int ks) { f0[j][ks] = lds_fragment(ax[ks] + j * 2048); };
+  auto read_w = [&](int i, int ks) { fw[i][ks] = lds_fragment((aw ^ ks * 64) + i * 2048); };
+  auto read_x0 = [&](int j, int ks) { f0[j][ks] = lds_fragment((ax ^ ks * 64) + j * 2048); };
   auto read_x1 = [&](int j, int ks) {  // (J0 == J1: the same rows, X1 - X0 on)
-    f1[j][ks] = lds_fragment((J0 == J1 ? ax[ks] + (X1 - X0) : ax1[ks]) + j * 2048);
+    f1[j][ks] = lds_fragment(((J0 == J1 ? ax + (X1 - X0) : ax1) ^ ks * 64) + j * 2048);
   };
 
   // Copies.  A wave instruction fills 8 rows of 128 bytes.
@@ -102,8 +103,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
   const uint16_t* xs;
   const uint16_t* ws;
   uint32_t xo[2 + C1];
-  const uint32_t wo = __umul24((uint32_t)(wave * 8 + (lane >> 3)), (uint32_t)K * 2u) +
-                      (uint32_t)copy_chunk<8>(lane, wave) * 16u;
+  uint32_t wo;
   // A copy of the lane index that the compiler cannot see through: what is
   // derived from it is computed where it is used and not kept in registers
   // over the main loop, which has none to spare.
@@ -111,6 +111,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     int l = lane;
     asm volatile("" : "+v"(l));
     return l;
+  };
+  // The addresses that stay the same over a tile but for the stage parity p;
+  // formed at its start so that they take no registers over the epilogue.
+  // With one register too many the allocator spilled wo, and the compiler
+  // then waited for every copy in flight where it was used again, in each
+  // K stage.
+  auto tile_addresses = [&](uint32_t p) {
+    const int l = opaque_lane();
+    const uint32_t ch = (uint32_t)swz<8>(l & 15, l >> 4) * 16u + p * BUF;
+    aw = lds + (uint32_t)wn0 * 128u + ch;
+    ax = lds + X0 + (uint32_t)(wave_m * R0) * 128u + ch;
+    ax1 = lds + X1 + (uint32_t)(wave_m * R1) * 128u + ch;
+    wo = __umul24((uint32_t)(wave * 8 + (l >> 3)), (uint32_t)K * 2u) +
+         (uint32_t)copy_chunk<8>(l, wave) * 16u;
   };
   auto point = [&]() {
     int tm_, tn_;
@@ -146,6 +160,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 
   int t = blockIdx.x;  // < n_tiles: the grid is never larger than the tile count
   point();
+  tile_addresses(0);
   // Without row factors the launch has one tile per workgroup: thread r
   // merges the statistics of row r, before the first copy (a wait for the
   // loads is then no wait for copies).
@@ -180,6 +195,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     tile_coords<ORDER>(t, n_tiles, tiles_n, &tm, &tn);
     const int m0 = tm * BM;
     const int n0 = tn * BN;
+    tile_addresses(p);
 
     // Per-feature vectors, wave w copying vector w, and the row factors;
     // published by the barriers of the tile's first stages, last read two
@@ -255,12 +271,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
       __syncthreads();
       // The next stage is read from the other parity.
       const uint32_t other = p ? 0u - BUF : BUF;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        aw[ks] += other;
-        ax[ks] += other;
-        ax1[ks] += other;
-      }
+      aw += other;
+      ax += other;
+      ax1 += other;
       const uint32_t go1 = lane_mask(go && !last);
       __builtin_amdgcn_sched_barrier(0);
       // Phase 1 (the fragments read at a tile's last stage are not used):
