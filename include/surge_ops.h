@@ -97,6 +97,15 @@ surge_status surge_op_linear_ln_noalloc(int64_t M, int32_t N, int32_t K, const u
 int32_t surge_op_linear_stats_width(int64_t M, int32_t N);
 
 /*
+ * The tile that the linear layer's launch takes for an [M, N] output of K
+ * inputs on a device of n_cus compute units, rows << 16 | features (host-only;
+ * 0 for shapes that the layer refuses).  Where N is not a multiple of the
+ * features, the last 128 take 128 x 128 tiles.  Every tile gives the same
+ * bits.
+ */
+int32_t surge_op_linear_tile(int64_t M, int32_t N, int32_t K, int32_t n_cus);
+
+/*
  * Packed varlen multi-head self-attention within each text:
  * out[rows of text i, head h] = softmax(Q_h K_h^T / sqrt(d_head)) V_h.
  * d_qkv bf16 [T, 3 n_heads d_head] (Q | K | V blocks, head h at columns

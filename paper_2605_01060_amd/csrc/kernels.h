@@ -74,6 +74,9 @@ hipError_t launch_linear(const uint16_t* X, const uint16_t* W, const float* bias
 // statistics, `parts` partials a row, by itself (ex.stats_in), so that
 // launch_ln_rows need not run before it.
 bool linear_merges_stats(int64_t M, int N, int K, int parts, int n_cus);
+// The tile of an [M, N] layer's launch on a device of n_cus compute units,
+// rows << 16 | features (see surge_op_linear_tile).
+int linear_tile(int64_t M, int N, int K, int n_cus);
 // Sets *n_cus to the current device's compute units unless it is positive.
 hipError_t resolve_cus(int* n_cus);
 // Features per statistics partial written by launch_linear for an [M, N]

@@ -6,7 +6,8 @@
 // Three tile families share the operand layout, the K order and the finish
 // of every output, and launch_linear picks one by the launch's tile counts:
 // small chunks (linear_ring.hip), 256 x 256 or 192 x 256 tiles
-// (linear_wide.hip), and the 128 x 128 tiles of this file in between and for N not a multiple of 256.
+// (linear_wide.hip), and the 128 x 128 tiles of this file in between and for
+// the odd last 128 features of an N that is not a multiple of 256.
 //
 // Tiling.  A workgroup computes 128 x 128 tiles of Y (tokens x features) with
 // four waves of 64 x 64 (16x16x32 bf16 MFMAs).  K is walked in 64-wide stages
@@ -359,29 +360,6 @@ static RingTile ring_tile(int64_t M, int N, int n_cus) {
   return RING_NONE;
 }
 
-// 256 x 256 or 192 x 256 tiles (one workgroup per CU), or 128 x 128 tiles
-// (two): the rows of the tile whose rounds take least.  The unit is a full
-// round of 128-wide tiles.  Those fill the chip by halves of a round and end
-// about 0.15 late; a round of 256-row tiles does twice the work in 1.5 + 134
-// / K units (the less, the more main loop there is per epilogue), and one of
-// 192-row tiles three quarters of that in 0.88 of the time (fewer MFMAs per
-// operand byte), but a begun round costs a whole one.  Measured (us, 128 /
-// 192 / 256): N = 2304, K = 768: M = 6144 28.8 / 39.5 / 25.0, 8192 34.6 /
-// 37.8 / 45.5, 10,000 42.3 / 38.6 / 43.9, 13,579 54.8 / 56.6 / 48.6; N = 768,
-// K = 3072: 8192 46.8 / 58.7 / 66.9, 13,579 81.8 / 66.8 / 74.1, 17,000 94.3 /
-// 122 / 73.6, 262,144 1,347 / 1,166 / 1,071.
-static int tile_rows(int64_t M, int N, int K, int n_cus) {
-  auto rounds = [&](int64_t bm, int bn) {
-    return (double)(((M + bm - 1) / bm * (N / bn) + n_cus - 1) / n_cus);
-  };
-  const double wide = 1.5 + 134.0 / K;
-  const double c128 = 0.5 * rounds(128, 128) + 0.15;
-  const double c192 = 0.88 * wide * rounds(192, 256);
-  const double c256 = wide * rounds(256, 256);
-  if (c192 < c256 && c192 < c128) return 192;
-  return c256 <= c128 ? 256 : 128;
-}
-
 int linear_stats_width(int64_t, int) { return STATS_WIDTH; }
 
 hipError_t resolve_cus(int* n_cus) {
@@ -392,26 +370,62 @@ hipError_t resolve_cus(int* n_cus) {
   return hipDeviceGetAttribute(n_cus, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
-// Which family a launch takes.  N is a multiple of 128: an odd one takes
-// 256-wide tiles over all but its last 128 features where that is most of
-// them and the launch is long: the rest reads X once more in a launch of its
-// own (N = 1152, K = 384: 311 -> 276 us at 265,000 rows, 115 -> 118 at
-// 100,000; N = 384, K = 1536: 406 -> 470 at 265,000).
+// Which family a launch takes: beyond the small chunks 256 x 256 or 192 x 256
+// tiles (one workgroup per CU) or 128 x 128 tiles (two), by the cost of their
+// rounds.  The unit is a full round of 128-wide tiles.  Those fill the chip by
+// halves of a round and end about 0.05 late; a round of 256-row tiles does
+// twice the work in 1.4 + 230 / (K + 350) units (the less, the more main loop
+// there is per epilogue: 1.45 at K = 4096, at most 1.84, where stores bound
+// both), and one of 192-row tiles three quarters of that in 0.82 of the time
+// (fewer MFMAs per operand byte), but a begun round costs a whole one, and
+// the first has 50 / K units of copies with no main loop to hide behind.
+// Fitted to 1,814 launches of N = 256 .. 4096, K = 64 .. 4096, M = 2500 ..
+// 262,144 timed under each family: the mean one takes 0.2 % longer than under
+// its best, the worst 14 %.
+// Measured (us, 128 / 192 / 256 rows):
+//   N = 2304, K = 768   M = 6144 28.8 / 39.5 / 25.0    8192 34.6 / 37.8 / 45.5
+//                       10,000 42.3 / 38.6 / 43.9      13,579 54.8 / 56.6 / 48.6
+//   N = 768, K = 3072   M = 8192 46.8 / 58.7 / 66.9    13,579 81.8 / 66.8 / 74.1
+//                       17,000 94.3 / 122 / 73.6       262,144 1,347 / 1,166 / 1,071
+//   N = 768, K = 256    M = 8192 8.0 / 10.3 / 11.8     262,144 162 / 144 / 133
+//   N = 2304, K = 64    M = 13,579 17.3 / 20.5 / 19.5  262,144 244 / 243 / 229.
+// An odd last 128 features take 128-wide tiles in a launch of their own, which
+// reads X once more and costs 0.45 units beside its rounds.  1,058 launches of
+// N = 384 .. 2432 are 0.1 % off their best in the mean (9 % at worst); all on
+// 128-wide tiles they are 1.9 % (43 %).  Measured (us, 128 / 128 and 256): N =
+// 1152, K = 64 M = 131,149 63.4 / 67.8, K = 384 65,000 75.9 / 70.6, K = 3072
+// 65,000 514 / 422; N = 640, K = 3072 20,000 104 / 118, 65,000 298 / 269.  With
+// one column of 256-wide tiles before them (N = 384) it never paid: K = 768 M =
+// 262,144 207 / 214, K = 1536 100,000 151 / 176.
 enum Family { FAMILY_RING, FAMILY_MID, FAMILY_WIDE, FAMILY_WIDE_AND_MID };
 struct Choice {
   Family family;
-  int rows;  // of a wide tile
+  int rows;  // of a tile, but for FAMILY_RING's
 };
 static Choice linear_family(int64_t M, int N, int K, int n_cus) {
   if (ring_tile(M, N, n_cus) != RING_NONE) return {FAMILY_RING, 0};
   // The wide tiles' copy offsets are products of 24-bit numbers.
-  if (K >= 1 << 23) return {FAMILY_MID, 0};
-  if (N % 256 == 0) {
-    const int rows = tile_rows(M, N, K, n_cus);
-    return {rows == 128 ? FAMILY_MID : FAMILY_WIDE, rows};
+  if (K >= 1 << 23) return {FAMILY_MID, 128};
+  auto rounds = [&](int64_t bm, int columns) {
+    return (double)(((M + bm - 1) / bm * columns + n_cus - 1) / n_cus);
+  };
+  auto mid = [&](int columns) { return 0.5 * rounds(128, columns) + 0.05; };
+  const double wide = std::min(1.4 + 230.0 / (K + 350), 1.84), start = 50.0 / K;
+  const double c256 = start + wide * rounds(256, N / 256);
+  if (N % 256 != 0) {
+    const bool split = N > 512 && c256 + mid(1) + 0.45 < mid(N / 128);
+    return split ? Choice{FAMILY_WIDE_AND_MID, 256} : Choice{FAMILY_MID, 128};
   }
-  const int64_t t256 = (M + 255) / 256 * (N / 256);
-  return {N > 1024 && t256 >= 8 * (int64_t)n_cus ? FAMILY_WIDE_AND_MID : FAMILY_MID, 256};
+  const double c128 = mid(N / 128), c192 = start + 0.82 * wide * rounds(192, N / 256);
+  if (c192 < c256 && c192 < c128) return {FAMILY_WIDE, 192};
+  return c256 <= c128 ? Choice{FAMILY_WIDE, 256} : Choice{FAMILY_MID, 128};
+}
+
+int linear_tile(int64_t M, int N, int K, int n_cus) {
+  const Choice c = linear_family(M, N, K, n_cus);
+  if (c.family != FAMILY_RING) return c.rows << 16 | (c.family == FAMILY_MID ? 128 : 256);
+  const RingTile t = ring_tile(M, N, n_cus);
+  return (t == RING_32x64 ? 32 : 64) << 16 | (t == RING_64x128 ? 128 : 64);
 }
 
 // The tiles merge statistics where that costs less than a row-factor launch

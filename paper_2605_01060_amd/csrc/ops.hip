@@ -297,6 +297,12 @@ surge_status surge_op_linear_ln_noalloc(int64_t M, int32_t N, int32_t K, const u
 
 int32_t surge_op_linear_stats_width(int64_t M, int32_t N) { return linear_stats_width(M, N); }
 
+int32_t surge_op_linear_tile(int64_t M, int32_t N, int32_t K, int32_t n_cus) {
+  if (M < 1 || M > (int64_t)INT32_MAX || N < 128 || N % 128 || K < 64 || K % 64 || n_cus < 1)
+    return 0;
+  return linear_tile(M, N, K, n_cus);
+}
+
 surge_status surge_op_attention(int64_t n_texts, const int64_t* cu, int32_t n_heads, int32_t d_head,
                                 const uint16_t* d_qkv, uint16_t* d_out, void* hip_stream) {
   clear_error();

@@ -95,6 +95,7 @@ _SIGNATURES = {
     "surge_op_linear_ln_noalloc": ([_I64, _I32, _I32, _P, _P, _P, _P, _I32, _P, _I32, _P, _P,
                                     _P, ctypes.c_float, _P, _P, _P], _I32),
     "surge_op_linear_stats_width": ([_I64, _I32], _I32),
+    "surge_op_linear_tile": ([_I64, _I32, _I32, _I32], _I32),
     "surge_op_attention": ([_I64, _P, _I32, _I32, _P, _P, _P], _I32),
     "surge_op_layernorm": ([_I64, _I32, _P, _P, _P, ctypes.c_float, _P, _P], _I32),
     "surge_op_pool_l2": ([_I64, _P, _I32, _P, _P, _P], _I32),
@@ -351,6 +352,12 @@ def surge_op_linear_ln_noalloc(M, N, K, x, w, bias, res, epilogue, stats_in, par
 
 def surge_op_linear_stats_width(M: int, N: int) -> int:
     return int(lib().surge_op_linear_stats_width(M, N))
+
+
+def surge_op_linear_tile(M: int, N: int, K: int, n_cus: int = 256):
+    """(rows, features) of the tile that an [M, N] layer's launch takes."""
+    tile = int(lib().surge_op_linear_tile(M, N, K, n_cus))
+    return tile >> 16, tile & 0xffff
 
 
 def surge_op_attention(cu_seqlens, n_heads, d_head, d_qkv, d_out, stream=None):
