@@ -270,6 +270,11 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
     for (int kt = 0; kt < nkt; ++kt) {
       read(smem + cur_buf * SSTAGE, 1);
       step(0);
+      // None of these MFMAs behind the barrier, where the next copies would
+      // wait for their issue: in launches of few tiles a stage is as long as
+      // its copies take (N = 768, K = 3072, us: M = 4000 35.2 -> 33.5, 7000
+      // 43.3 -> 40.7; N = 384, K = 1536, 265,000 rows 480 -> 468).
+      __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this stage's reads are done
       __syncthreads();
@@ -381,22 +386,21 @@ hipError_t resolve_cus(int* n_cus) {
 // the first has 50 / K units of copies with no main loop to hide behind.
 // Fitted to 1,814 launches of N = 256 .. 4096, K = 64 .. 4096, M = 2500 ..
 // 262,144 timed under each family: the mean one takes 0.2 % longer than under
-// its best, the worst 14 %.
-// Measured (us, 128 / 192 / 256 rows):
-//   N = 2304, K = 768   M = 6144 28.8 / 39.5 / 25.0    8192 34.6 / 37.8 / 45.5
-//                       10,000 42.3 / 38.6 / 43.9      13,579 54.8 / 56.6 / 48.6
-//   N = 768, K = 3072   M = 8192 46.8 / 58.7 / 66.9    13,579 81.8 / 66.8 / 74.1
-//                       17,000 94.3 / 122 / 73.6       262,144 1,347 / 1,166 / 1,071
-//   N = 768, K = 256    M = 8192 8.0 / 10.3 / 11.8     262,144 162 / 144 / 133
-//   N = 2304, K = 64    M = 13,579 17.3 / 20.5 / 19.5  262,144 244 / 243 / 229.
+// its best, the worst 13 %.  Measured (us, 128 / 192 / 256 rows):
+//   N = 2304, K = 768   M = 6144 28.0 / 37.7 / 24.2    8192 35.6 / 38.5 / 44.0
+//                       10,000 42.5 / 40.7 / 44.7      13,579 56.8 / 56.7 / 48.8
+//   N = 768, K = 3072   M = 8192 43.4 / 57.7 / 65.4    13,579 79.5 / 64.2 / 67.1
+//                       17,000 87.6 / 120 / 72.2       262,144 1,301 / 1,149 / 1,033
+//   N = 768, K = 256    M = 8192 8.0 / 10.2 / 11.7     262,144 153 / 146 / 133
+//   N = 2304, K = 64    M = 13,579 17.2 / 20.6 / 19.5  262,144 243 / 243 / 229.
 // An odd last 128 features take 128-wide tiles in a launch of their own, which
 // reads X once more and costs 0.45 units beside its rounds.  1,058 launches of
-// N = 384 .. 2432 are 0.1 % off their best in the mean (9 % at worst); all on
-// 128-wide tiles they are 1.9 % (43 %).  Measured (us, 128 / 128 and 256): N =
-// 1152, K = 64 M = 131,149 63.4 / 67.8, K = 384 65,000 75.9 / 70.6, K = 3072
-// 65,000 514 / 422; N = 640, K = 3072 20,000 104 / 118, 65,000 298 / 269.  With
-// one column of 256-wide tiles before them (N = 384) it never paid: K = 768 M =
-// 262,144 207 / 214, K = 1536 100,000 151 / 176.
+// N = 384 .. 2432 are 0.1 % off their best in the mean (8 % at worst); all on
+// 128-wide tiles they are 1.4 % (47 %).  Measured (us, 128 / 128 and 256): N =
+// 1152, K = 64 M = 140,000 67.2 / 71.4, K = 3072 55,000 406 / 382; N = 640, K =
+// 3072 20,781 97.2 / 117, 55,000 255 / 244.  With one column of 256-wide tiles
+// before them (N = 384) it never paid: K = 768 M = 262,144 201 / 212, K = 1536
+// 100,000 151 / 179.
 enum Family { FAMILY_RING, FAMILY_MID, FAMILY_WIDE, FAMILY_WIDE_AND_MID };
 struct Choice {
   Family family;

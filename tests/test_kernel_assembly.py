@@ -1,4 +1,4 @@
-"""What the compiler made of the kernels' registers, from its assembly.
+"""What the compiler made of the kernels, from its assembly.
 
 The linear kernels wait for their inline-assembly copies themselves; the
 compiler does not know of those copies.  A register that it spills inside
@@ -69,3 +69,19 @@ def test_no_wait_of_the_compilers_between_the_wide_tiles_mfmas(assembly):
             mfmas += op.startswith("v_mfma")
             waits += not inline and op.startswith("s_waitcnt") and "vmcnt" in op
     assert checked >= 14 * 48
+
+
+def test_nothing_before_the_128_wide_tiles_copies(assembly):
+    """In the K loop the barrier that frees a stage's buffer is followed by
+    the copies into it, with no MFMAs to issue first."""
+    loops = 0
+    for name, _, body in _kernels(assembly["linear.hip"]):
+        for block in body.split("\n.LBB"):
+            lines = [line.strip() for line in block.split("\n")]
+            if not any(op.startswith("v_mfma") for op in lines) or "s_barrier" not in lines:
+                continue
+            after = lines[lines.index("s_barrier"):]
+            copy = next(i for i, op in enumerate(after) if op.startswith("global_load_lds"))
+            assert not any(op.startswith("v_mfma") for op in after[:copy]), name
+            loops += 1
+    assert loops >= 10

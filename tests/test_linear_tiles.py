@@ -8,21 +8,22 @@ from paper_2605_01060_amd import surge as S
 # (M, N, K), us with 128-wide, 192-row and 256-row tiles (for N not a multiple
 # of 256 the last 128 features are 128-wide in each)
 MEASURED = [
-    ((262_144, 768, 64), 85.3, 86.7, 82.7), ((262_144, 2304, 64), 244.1, 243.4, 229.2),
-    ((13_579, 2304, 64), 17.3, 20.5, 19.5), ((30_000, 1024, 64), 17.4, 20.3, 19.7),
-    ((262_144, 768, 256), 162.1, 144.0, 133.3), ((100_000, 2304, 256), 178.3, 162.8, 150.6),
-    ((262_144, 3072, 128), 413.1, 396.1, 369.5), ((100_000, 1024, 384), 102.5, 97.6, 94.6),
-    ((8192, 768, 256), 8.0, 10.3, 11.8), ((13_579, 512, 384), 9.8, 12.2, 14.2),
-    ((75_000, 256, 4096), 231.7, 182.2, 213.3), ((40_000, 512, 4096), 210.0, 170.8, 187.9),
-    ((6144, 2304, 768), 28.8, 39.5, 25.0), ((8192, 2304, 768), 34.6, 37.8, 45.5),
-    ((10_000, 2304, 768), 42.3, 38.6, 43.9), ((13_579, 2304, 768), 54.8, 56.6, 48.6),
-    ((8192, 768, 3072), 46.8, 58.7, 66.9), ((13_579, 768, 3072), 81.8, 66.8, 74.1),
-    ((17_000, 768, 3072), 94.3, 122.0, 73.6), ((262_144, 768, 3072), 1347.0, 1166.0, 1071.0),
+    ((262_144, 768, 64), 85.1, 87.4, 81.5), ((262_144, 2304, 64), 243.4, 242.8, 229.0),
+    ((13_579, 2304, 64), 17.2, 20.6, 19.5), ((30_000, 1024, 64), 17.3, 20.4, 19.7),
+    ((262_144, 768, 256), 153.2, 145.6, 132.5), ((100_000, 2304, 256), 168.5, 161.6, 150.1),
+    ((262_144, 3072, 128), 410.2, 392.2, 369.2), ((100_000, 1024, 384), 101.3, 99.1, 97.5),
+    ((8192, 768, 256), 8.0, 10.2, 11.7), ((13_579, 512, 384), 9.8, 12.2, 14.3),
+    ((75_000, 256, 4096), 231.9, 183.4, 213.9), ((40_000, 512, 4096), 211.3, 172.5, 188.3),
+    ((6144, 2304, 768), 28.0, 37.7, 24.2), ((8192, 2304, 768), 35.6, 38.5, 44.0),
+    ((10_000, 2304, 768), 42.5, 40.7, 44.7), ((13_579, 2304, 768), 56.8, 56.7, 48.8),
+    ((8192, 768, 3072), 43.4, 57.7, 65.4), ((13_579, 768, 3072), 79.5, 64.2, 67.1),
+    ((17_000, 768, 3072), 87.6, 120.0, 72.2), ((262_144, 768, 3072), 1300.8, 1148.5, 1032.9),
     # an odd number of 128 features
-    ((131_149, 1152, 64), 63.4, 67.2, 67.8), ((65_000, 1152, 384), 75.9, 77.2, 70.6),
-    ((65_000, 1152, 3072), 513.8, 465.9, 421.6), ((20_000, 640, 3072), 103.9, 113.6, 118.5),
-    ((65_000, 640, 3072), 298.2, 291.8, 269.0), ((65_000, 896, 768), 100.4, 97.8, 91.2),
-    ((262_144, 384, 768), 206.8, 233.6, 213.5), ((100_000, 384, 1536), 151.4, 190.6, 175.7),
+    ((140_000, 1152, 64), 67.2, 75.7, 71.4), ((55_000, 1152, 384), 68.1, 69.3, 69.8),
+    ((55_000, 1152, 3072), 406.1, 398.4, 381.7), ((75_000, 1152, 3072), 568.4, 577.3, 525.0),
+    ((20_781, 640, 3072), 97.2, 112.2, 117.4), ((55_000, 640, 3072), 254.9, 272.3, 244.3),
+    ((55_000, 896, 768), 84.3, 91.9, 87.9), ((75_000, 640, 3072), 333.6, 400.0, 372.8),
+    ((262_144, 384, 768), 201.2, 230.1, 212.0), ((100_000, 384, 1536), 151.4, 194.1, 178.5),
 ]
 
 
