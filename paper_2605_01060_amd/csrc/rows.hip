@@ -184,9 +184,9 @@ __global__ __launch_bounds__(256) void upload_kernel(const uint4* __restrict__ s
 // Rows as in the embedding: LPR lanes a row, a wave's trips of R rows each,
 // the next trip's chunks fetched before the current rows are normalised (a
 // wave reads and writes rows of its own only, so y may be x).  Bound by HBM.
-// Against one row per wave, us per call of 107,000 rows (about 12 of them the
-// host's): d = 768 89.7 -> 62.9, 384 48.6 -> 37.6, 1024 94.3 -> 77.6, 128
-// 44.2 -> 21.5; one row 14.5 -> 13.5.
+// Against one row per wave, us per call of 100,000 / 300,000 rows (about 12 of
+// them the host's): d = 768 78.9 -> 56.1 / 202 -> 161, 384 40.6 -> 34.8 / 124
+// -> 77.6, 1024 84.7 -> 70.6 / 222 -> 209, 128 38.7 -> 20.3 / 87.1 -> 33.6.
 template <int LPR, int C, bool STREAM_OUT>
 __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t* __restrict__ x,
                                                         const float* __restrict__ gamma,
@@ -369,9 +369,11 @@ hipError_t launch_layernorm(const uint16_t* x, const float* gamma, const float* 
                             uint16_t* y, int64_t M, int d, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
   const int lpr = lanes_per_row(d), rows = 4 * 64 / lpr;  // rows of a workgroup's trip
-  // One trip while workgroups are few; eight, for gamma and beta's sake, once
-  // 2,048 workgroups remain.
-  const int trips = (int)std::min<int64_t>(std::max<int64_t>(M / (rows * 2048), 1), 8);
+  // Two trips, for gamma and beta's sake, once they leave 2,048 workgroups:
+  // more keep rows of too many places in flight (300,000 rows, 1 / 2 / 3 / 4 /
+  // 8 trips, us: d = 1024 220 / 209 / 220 / 236 / 245, 768 164 / 161 / 168 /
+  // 174 / 184, 384 75.0 / 77.6 / 78.6 / 79.4 / 81.3).
+  const int trips = M >= (int64_t)rows * 4096 ? 2 : 1;
   const dim3 grid((unsigned)((M + rows * trips - 1) / (rows * trips)));
   const bool stream_out = M * d * 2 > STREAM_OUT_BYTES;
 #define SURGE_LAYERNORM(L, C)                                                                   \

@@ -540,10 +540,11 @@ def test_embed_ln_every_width(d):
 
 
 @pytest.mark.parametrize("d", [8, 120, 136, 384, 520, 776, 1016, 1024])
-@pytest.mark.parametrize("M", [1, 33, 40_003])
+@pytest.mark.parametrize("M", [1, 33, 40_003, 70_003])
 def test_layernorm_lane_layouts(d, M):
     """Chunk counts that leave lanes idle in either lane layout, calls of one
-    trip per wave and of several, and y written over x."""
+    trip per wave and of two (from 32,768 rows for d > 512, from 65,536 up to
+    512), and y written over x."""
     torch = torch_cuda()
     g = torch.Generator(device="cuda").manual_seed(d + M)
     x = torch.randn(M, d, generator=g, device="cuda").bfloat16()
