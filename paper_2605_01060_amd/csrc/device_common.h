@@ -237,12 +237,11 @@ __device__ __forceinline__ float2 ln_row_factors(Part part, int parts, float eps
 // GELU, z Phi(z) = max(z, 0) - |z| Phi(-|z|), both signs of z alike.  The
 // normal tail is taken as Phi(-x) = 2^P(x) with P of degree 7, the minimax
 // fit of log2 Phi(-x) on [0, 6] in the weight x Phi(-x) that its error has in
-// GELU (5.8e-8), under the condition P(x) < -28 - (x - 6) / 2 beyond, so that
-// large |z| give 0.  In fp32 the error of GELU is at most 2.9e-7 (4.5e-8 rms
-// on normal z).  Seven FMAs and one exponential; the rational form of
-// Abramowitz & Stegun 7.1.28 it replaces took three instruction slots of
-// sixteen more for 7.1e-7 (1.5e-7 rms), in the GEMM epilogues that the VALU
-// bounds.
+// GELU (6.1e-8), with P(x) < -27.99 - (x - 6) / 2 beyond, so that large |z|
+// give 0.  In fp32 the error of GELU is at most 3e-7 (4.5e-8 rms on normal z).
+// Seven FMAs and one exponential, 13 instruction slots with the sign handling
+// against 16 of the rational form of Abramowitz & Stegun 7.1.28 that it
+// replaces (7.1e-7, 1.5e-7 rms), in GEMM epilogues that the VALU bounds.
 __device__ __forceinline__ float gelu_erf(float z) {
   const float az = fabsf(z);
   float p = fmaf(-6.83212739e-7f, az, 4.04779173e-5f);
