@@ -63,19 +63,6 @@
 namespace surge {
 namespace {
 
-// Wait until at most `later` stages' copies (CPS instructions each) issued
-// after the one needed next are still in flight.  The vector memory counter
-// retires a wave's loads in issue order.
-template <int CPS>
-__device__ __forceinline__ void wait_copies(int later) {
-  if (later <= 0)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if (later == 1)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPS) : "memory");
-  else
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CPS) : "memory");
-}
-
 // With MERGE the rows' LayerNorm factors come from the statistics partials
 // (ex.stats_in): lane r of a wave loads those of the wave's row r at the
 // tile's start, so that their latency hides behind the main loop, and merges
@@ -179,9 +166,9 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
   issue(1);
   advance();
   if (second)
-    wait_copies<XI + WI>(1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(XI + WI) : "memory");
   else
-    wait_copies<XI + WI>(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
   constexpr int S = BK / 32;   // 32-wide MFMA steps per stage
@@ -325,24 +312,26 @@ hipError_t launch_mid(const uint16_t* X, const uint16_t* W, const float* bias, c
   const int n_tiles = (int)(tiles_m * tiles_n);
   const dim3 grid((unsigned)std::min<int64_t>(n_tiles, (int64_t)ex.n_cus * PER_CU));
   const dim3 block(256);
-  const bool merge = !ex.rows_in;
-#define SURGE_LAUNCH_EPI(E, O)                                                                  \
-  if (merge && (E == EPI_FOLD || E == EPI_FOLD_GELU || E == EPI_LNRES_STATS))                   \
-    hipLaunchKernelGGL((linear_bf16_kernel<E, O, true>), grid, block, 0, stream, X, W, bias, R, \
-                       Y, (int)M, N, K, tiles_n, n_tiles, ex);                                  \
-  else                                                                                          \
-    hipLaunchKernelGGL((linear_bf16_kernel<E, O, false>), grid, block, 0, stream, X, W, bias,   \
-                       R, Y, (int)M, N, K, tiles_n, n_tiles, ex)
+  // Only the epilogues with LayerNorm factors have a MERGE kernel.
+#define SURGE_LAUNCH(E, O, MERGE)                                                               \
+  hipLaunchKernelGGL((linear_bf16_kernel<E, O, MERGE>), grid, block, 0, stream, X, W, bias, R, Y, \
+                     (int)M, N, K, tiles_n, n_tiles, ex)
+#define SURGE_LAUNCH_FACTORS(E, O)   \
+  if (ex.rows_in)                    \
+    SURGE_LAUNCH(E, O, false);       \
+  else                               \
+    SURGE_LAUNCH(E, O, true)
   switch (epi) {
-    case EPI_BIAS: SURGE_LAUNCH_EPI(EPI_BIAS, ORDER_ROW_GROUPS); break;
-    case EPI_BIAS_GELU: SURGE_LAUNCH_EPI(EPI_BIAS_GELU, ORDER_FEATURE_HALVES); break;
-    case EPI_BIAS_RESIDUAL: SURGE_LAUNCH_EPI(EPI_BIAS_RESIDUAL, ORDER_ROW_GROUPS); break;
-    case EPI_FOLD: SURGE_LAUNCH_EPI(EPI_FOLD, ORDER_ROW_GROUPS); break;
-    case EPI_FOLD_GELU: SURGE_LAUNCH_EPI(EPI_FOLD_GELU, ORDER_FEATURE_HALVES); break;
-    case EPI_RES_STATS: SURGE_LAUNCH_EPI(EPI_RES_STATS, ORDER_ROW_GROUPS); break;
-    default: SURGE_LAUNCH_EPI(EPI_LNRES_STATS, ORDER_ROW_GROUPS); break;
+    case EPI_BIAS: SURGE_LAUNCH(EPI_BIAS, ORDER_ROW_GROUPS, false); break;
+    case EPI_BIAS_GELU: SURGE_LAUNCH(EPI_BIAS_GELU, ORDER_FEATURE_HALVES, false); break;
+    case EPI_BIAS_RESIDUAL: SURGE_LAUNCH(EPI_BIAS_RESIDUAL, ORDER_ROW_GROUPS, false); break;
+    case EPI_FOLD: SURGE_LAUNCH_FACTORS(EPI_FOLD, ORDER_ROW_GROUPS); break;
+    case EPI_FOLD_GELU: SURGE_LAUNCH_FACTORS(EPI_FOLD_GELU, ORDER_FEATURE_HALVES); break;
+    case EPI_RES_STATS: SURGE_LAUNCH(EPI_RES_STATS, ORDER_ROW_GROUPS, false); break;
+    default: SURGE_LAUNCH_FACTORS(EPI_LNRES_STATS, ORDER_ROW_GROUPS); break;
   }
-#undef SURGE_LAUNCH_EPI
+#undef SURGE_LAUNCH_FACTORS
+#undef SURGE_LAUNCH
   return hipGetLastError();
 }
 
