@@ -105,22 +105,25 @@ def test_tiny_invariant_to_composition_and_chunking():
 
 
 def test_bge_invariant_across_tile_configurations():
-    """bge shapes (d = 768): a chunk of fewer than 8192 tokens runs the
-    128 x 128 GEMM tiles, a larger one the 256 x 256 tiles; the folded
-    LayerNorms' row statistics are built from the same 64-feature partials
-    in both, so every text's embedding is bit-identical either way."""
+    """bge shapes (d = 768): the layers of a chunk of 2,048 tokens take 128 x
+    128 GEMM tiles or smaller ones, those of a large chunk 192 x 256 and 256 x
+    256 tiles too; the folded LayerNorms' row statistics are built from the
+    same 64-feature partials in all, so every text's embedding is
+    bit-identical either way."""
     import dataclasses
     torch = torch_cuda()
     spec = dataclasses.replace(W.WORKLOADS["bge"], n_texts=400, n_parts=8)
     wl = W.make_workload(spec)
     sh = spec.encoder
     weights = W.make_weights(sh, seed=spec.seed)
-    assert wl.n_tokens > 2 * 8192
-    big = S.Encoder(desc_of(sh), weight_list(sh, weights), 1 << 16)  # one chunk, 256-wide tiles
+    layers = ((2304, 768), (768, 768), (3072, 768), (768, 3072))
+    assert {(192, 256), (256, 256)} <= {S.surge_op_linear_tile(wl.n_tokens, *nk) for nk in layers}
+    assert all(S.surge_op_linear_tile(2048, *nk) <= (128, 128) for nk in layers)
+    big = S.Encoder(desc_of(sh), weight_list(sh, weights), 1 << 16)  # one chunk
     a, _ = _encode_all(torch, big, wl, sh.d_model, wl.n_texts, 0)
     b, nb = _encode_all(torch, big, wl, sh.d_model, 50, 80)  # small SuperBatches
     big.close()
-    small = S.Encoder(desc_of(sh), weight_list(sh, weights), 4096)  # chunks < 8192 tokens
+    small = S.Encoder(desc_of(sh), weight_list(sh, weights), 2048)  # small chunks
     c, _ = _encode_all(torch, small, wl, sh.d_model, wl.n_texts, 0)
     small.close()
     assert nb > 4

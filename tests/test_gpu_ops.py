@@ -38,7 +38,7 @@ LINEAR_SHAPES = [
     (1152, 384, 130), (384, 384, 257), (1536, 384, 96), (384, 1536, 300),   # MiniLM
     (2304, 768, 255), (768, 768, 128), (3072, 768, 513), (768, 3072, 200),  # bge
     (3072, 1024, 64), (1024, 1024, 100), (4096, 1024, 37), (1024, 4096, 129),  # large
-    # one 64-wide K stage (a tile's first stage is also its last), both tile configurations
+    # one 64-wide K stage (a tile's first stage is also its last), 32 x 64 and 128 x 128 tiles
     (128, 64, 300), (256, 64, 8200),
 ]
 
@@ -95,9 +95,9 @@ def _partials(v64, width):
     return np.ascontiguousarray(st.transpose(1, 0, 2))
 
 
-LN_SHAPES = [  # (N, K, M): small tiles with ragged M, and >= 8192 rows for 256 x 256 tiles
+LN_SHAPES = [  # (N, K, M): small tiles with ragged M, then 128-wide, 192-row and 256-row ones
     (2304, 768, 255), (3072, 768, 513), (768, 768, 128), (768, 3072, 200), (1152, 384, 130),
-    (768, 768, 9000), (3072, 768, 8193),
+    (768, 768, 9000), (768, 768, 13_579), (3072, 768, 8193),
     (256, 64, 8200), (128, 64, 77),  # a single K stage per tile
 ]
 
@@ -377,118 +377,122 @@ def test_pool_l2(d):
         assert np.max(np.abs(got[i] - ref)) < 2e-6, i
 
 
-@pytest.mark.parametrize("N,K", [(384, 64), (384, 320), (1152, 384), (384, 1536)])
-@pytest.mark.parametrize("epi", range(7))
-def test_small_calls_match_the_large_call_bit_for_bit(N, K, epi):
-    """The first M rows of a large call against a call of M rows: M at the
-    edges of the 32- and 64-row tiles and on both sides of the sizes where
-    the tile changes, odd and even numbers of K halves.  Every tile takes the
-    same MFMAs in the same order, so outputs and statistics are equal."""
-    torch = torch_cuda()
-    g = torch.Generator(device="cuda").manual_seed(N + K + epi)
-    m = 128 * (512 // (N // 128) + 1) + 5  # past every one-tile-per-CU size
-
-    def randn(*dims):
-        return torch.randn(dims, generator=g, device="cuda")
-
-    x, w, b = randn(m, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
-    res = randn(m, N).bfloat16() if epi in (2, 5, 6) else None
-    raw = (res if epi == 6 else x).float().view(m, -1, 64)
-    st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)  # [m, parts, 2]
-    parts = st_in.shape[1]
-    vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N)) if epi >= 3 else (None,) * 3
-
-    def call(rows):
-        y = torch.full((rows, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-        st = torch.zeros((N // 64, rows, 2), device="cuda")
-        S.surge_op_linear_ln(rows, N, K, x, w, b, res, epi,
-                             st_in[:rows].transpose(0, 1).contiguous(), parts, *vecs, 1e-12, st, y)
-        return y, st
-
-    y, st = call(m)
-    assert not torch.isnan(y).any()
-    tiles64, tiles128 = 256 // (N // 64) * 64, 256 // (N // 128) * 64
-    for rows in (1, 31, 32, 33, 64, 65, tiles64 // 2, tiles64 // 2 + 1, tiles64, tiles64 + 1,
-                 tiles128, tiles128 + 1):
-        ys, ss = call(rows)
-        assert torch.equal(ys, y[:rows]), rows
-        assert torch.equal(ss, st[:, :rows]), rows
+def _tile(torch, M, N, K):
+    """(rows, features) of the tile that the launch takes on this device."""
+    return S.surge_op_linear_tile(M, N, K, torch.cuda.get_device_properties(0).multi_processor_count)
 
 
-@pytest.mark.parametrize("N,epi", [(1152, 3), (1152, 6), (1024, 4), (768, 5)])
-def test_tile_families_match_bit_for_bit(N, epi):
-    """256-wide tiles (for N = 1152 with a last 128 features of 128-wide ones)
-    against 128-wide tiles of the same rows, in chunks of 5,000: outputs and
-    statistics are equal, ragged last rows included."""
-    torch = torch_cuda()
-    K = 128
-    g = torch.Generator(device="cuda").manual_seed(N + epi)
-    M = 8 * 256 * 256 // (N // 256) + 77
+def _layer(torch, M, N, K, epi):
+    """call(a, e): outputs and statistics of a random layer's rows a .. e - 1,
+    in a call of their own."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K + epi)
 
     def randn(*dims):
         return torch.randn(dims, generator=g, device="cuda")
 
     x, w, b = randn(M, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
-    res = randn(M, N).bfloat16() if epi in (5, 6) else None
+    res = randn(M, N).bfloat16() if epi in (2, 5, 6) else None
     raw = (res if epi == 6 else x).float().view(M, -1, 64)
-    st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)
-    vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N))
+    st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)  # [M, parts, 2]
+    vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N)) if epi >= 3 else (None,) * 3
 
     def call(a, e):
-        y = torch.empty((e - a, N), dtype=torch.bfloat16, device="cuda")
+        y = torch.full((e - a, N), float("nan"), dtype=torch.bfloat16, device="cuda")
         st = torch.zeros((N // 64, e - a, 2), device="cuda")
         S.surge_op_linear_ln(e - a, N, K, x[a:e], w, b, None if res is None else res[a:e], epi,
                              st_in[a:e].transpose(0, 1).contiguous(), st_in.shape[1], *vecs, 1e-12,
                              st, y)
         return y, st
 
+    return call
+
+
+def _assert_rows_match(torch, call, M, rows):
+    """The whole call against calls of `rows` rows at its start, middle and end."""
     y, st = call(0, M)
-    for a in (0, M // 2 // 8 * 8, M - 5000 + M % 8):
-        ys, ss = call(a, a + min(5000, M - a))
-        n = ys.shape[0]
-        assert torch.equal(ys, y[a:a + n]), a
-        if epi >= 5:
-            assert torch.equal(ss, st[:, a:a + n]), a
+    assert not torch.isnan(y).any()
+    for a in (0, M // 2 // 8 * 8, (M - rows) // 8 * 8):
+        ys, ss = call(a, a + rows)
+        assert torch.equal(ys, y[a:a + rows]), a
+        assert torch.equal(ss, st[:, a:a + rows]), a
+
+
+@pytest.mark.parametrize("N,K", [(384, 64), (384, 320), (1152, 384), (384, 1536)])
+@pytest.mark.parametrize("epi", range(7))
+def test_small_calls_match_the_large_call_bit_for_bit(N, K, epi):
+    """The first M rows of a large call of 128-wide tiles against a call of M
+    rows: M at the edges of the 32- and 64-row tiles and on both sides of the
+    sizes where the tile changes, odd and even numbers of K halves.  Every tile
+    takes the same MFMAs in the same order, so outputs and statistics are equal."""
+    torch = torch_cuda()
+    m = 128 * (512 // (N // 128) + 1) + 5  # past every one-tile-per-CU size
+    call = _layer(torch, m, N, K, epi)
+    y, st = call(0, m)
+    assert not torch.isnan(y).any()
+    tiles64, tiles128 = 256 // (N // 64) * 64, 256 // (N // 128) * 64
+    sizes = (1, 31, 32, 33, 64, 65, tiles64 // 2, tiles64 // 2 + 1, tiles64, tiles64 + 1,
+             tiles128, tiles128 + 1)
+    assert _tile(torch, m, N, K) == (128, 128)
+    assert {_tile(torch, rows, N, K) for rows in sizes} \
+        == {(32, 64), (64, 64), (64, 128), (128, 128)}
+    for rows in sizes:
+        ys, ss = call(0, rows)
+        assert torch.equal(ys, y[:rows]), rows
+        assert torch.equal(ss, st[:, :rows]), rows
+
+
+# (M, N, K) of persistent launches, four to ten tiles per workgroup; K of one,
+# two and more stages; for N = 1152 the last 128 features are 128-wide tiles
+WIDE_256 = [(130_003, 768, 64), (130_003, 1152, 128), (160_003, 1152, 384), (60_003, 1024, 512),
+            (70_001, 768, 768)]
+WIDE_192 = [(10_001, 2304, 768), (16_003, 2304, 768), (30_001, 768, 768)]
+
+
+@pytest.mark.parametrize("M,N,K", WIDE_256)
+@pytest.mark.parametrize("epi", range(7))
+def test_tile_families_match_bit_for_bit(M, N, K, epi):
+    """256-row tiles over several rounds against calls of 5,000 rows, which take
+    128-wide tiles: outputs and statistics are equal, ragged last rows
+    included."""
+    torch = torch_cuda()
+    assert _tile(torch, M, N, K) == (256, 256)
+    assert _tile(torch, 5000, N, K) == (128, 128)
+    _assert_rows_match(torch, _layer(torch, M, N, K, epi), M, 5000)
+
+
+@pytest.mark.parametrize("M,N,K", WIDE_192)
+@pytest.mark.parametrize("epi", range(7))
+def test_192_row_tiles_over_rounds_match_bit_for_bit(M, N, K, epi):
+    """Persistent launches of 192-row tiles (two and three tiles per workgroup,
+    row factors from their kernel) against calls of 3,000 rows."""
+    torch = torch_cuda()
+    assert _tile(torch, M, N, K) == (192, 256)
+    assert _tile(torch, 3000, N, K)[1] < 256
+    _assert_rows_match(torch, _layer(torch, M, N, K, epi), M, 3000)
 
 
 @pytest.mark.parametrize("epi", range(7))
 @pytest.mark.parametrize("N,M", [(256, 192 * 200 + 5), (512, 192 * 127 + 191)])
 def test_192_row_tiles_match_bit_for_bit(N, M, epi):
     """Row counts that fill one round of 192 x 256 tiles (even and odd numbers
-    of K stages, ragged last tile) against calls of 3,000 rows."""
+    of K stages, ragged last tile), whose workgroups merge their rows'
+    statistics, against calls of 3,000 rows."""
     torch = torch_cuda()
-    g = torch.Generator(device="cuda").manual_seed(N + epi)
     for K in (512, 576):
-        def randn(*dims):
-            return torch.randn(dims, generator=g, device="cuda")
-
-        x, w, b = randn(M, K).bfloat16(), (randn(N, K) * 0.05).bfloat16(), randn(N)
-        res = randn(M, N).bfloat16() if epi in (2, 5, 6) else None
-        raw = (res if epi == 6 else x).float().view(M, -1, 64)
-        st_in = torch.stack([raw.mean(2), raw.var(2, unbiased=False)], 2)
-        vecs = (randn(N), 1 + 0.1 * randn(N), 0.1 * randn(N)) if epi >= 3 else (None,) * 3
-
-        def call(a, e):
-            y = torch.empty((e - a, N), dtype=torch.bfloat16, device="cuda")
-            st = torch.zeros((N // 64, e - a, 2), device="cuda")
-            S.surge_op_linear_ln(e - a, N, K, x[a:e], w, b, None if res is None else res[a:e], epi,
-                                 st_in[a:e].transpose(0, 1).contiguous(), st_in.shape[1], *vecs,
-                                 1e-12, st, y)
-            return y, st
-
-        y, st = call(0, M)
-        for a in (0, M // 2 // 8 * 8, (M - 3000) // 8 * 8):
-            ys, ss = call(a, a + 3000)
-            assert torch.equal(ys, y[a:a + 3000]), (K, a)
-            assert epi < 5 or torch.equal(ss, st[:, a:a + 3000]), (K, a)
+        assert _tile(torch, M, N, K) == (192, 256)
+        _assert_rows_match(torch, _layer(torch, M, N, K, epi), M, 3000)
 
 
-@pytest.mark.parametrize("M", [24, 2080, 5003, 13_579])
-def test_statistics_updated_in_place(M):
-    """Residual statistics read from and written to one buffer, in the sizes
-    of every tile family: the same as with two buffers."""
+@pytest.mark.parametrize("M,K,tile", [(24, 128, (32, 64)), (1300, 128, (64, 64)),
+                                      (2080, 128, (64, 128)), (5003, 128, (128, 128)),
+                                      (13_579, 3072, (192, 256)), (17_000, 3072, (256, 256))])
+def test_statistics_updated_in_place(M, K, tile):
+    """Residual statistics read from and written to one buffer, in one launch of
+    every tile (the wide ones of one tile per workgroup, which merge statistics
+    themselves unless one buffer holds both): the same as with two buffers."""
     torch = torch_cuda()
-    N, K = 768, 128
+    N = 768
+    assert _tile(torch, M, N, K) == tile
     g = torch.Generator(device="cuda").manual_seed(M)
 
     def randn(*dims):
@@ -506,6 +510,7 @@ def test_statistics_updated_in_place(M):
             out = a if in_place else torch.zeros_like(a)
             y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
             op(M, N, K, x, w, b, res, 6, a, N // 64, None, gamma, beta, 1e-12, out, y)
+            torch.cuda.synchronize()
             got.append((y, out))
         assert torch.equal(got[0][0], got[1][0])
         assert torch.equal(got[0][1], got[1][1])
