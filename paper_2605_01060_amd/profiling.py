@@ -72,16 +72,17 @@ def name_class(name: str) -> Optional[str]:
 
 def dispatch_classes(names: List[str]) -> List[Optional[str]]:
     """Kernel class of every dispatch, given the names in dispatch order: a
-    residual-epilogue GEMM is FFN2 when the linear dispatch before it was
-    FFN1 (the FFN output), and the O-projection otherwise."""
+    residual-epilogue GEMM is FFN2 where an FFN1 dispatch came after the last
+    attention, and the O-projection otherwise (a layer may take two
+    dispatches, the second of its last 128 features)."""
     out: List[Optional[str]] = []
-    last_linear = None
+    last = None
     for n in names:
         c = name_class(n)
         if c == "residual":
-            c = "ffn2" if last_linear == "ffn1" else "oproj"
-        if c in ("qkv", "ffn1", "oproj", "ffn2"):
-            last_linear = c
+            c = "ffn2" if last == "ffn1" else "oproj"
+        if c in ("qkv", "attn", "ffn1"):
+            last = c
         out.append(c)
     return out
 

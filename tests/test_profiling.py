@@ -42,6 +42,15 @@ def test_residual_gemms_told_apart_by_dispatch_order():
         "qkv", "attn", "oproj", "ffn1", "ffn2", None]
 
 
+def test_layers_of_two_dispatches_keep_their_class():
+    """A layer whose last 128 features have a launch of their own."""
+    qkv, res, ffn1 = (LIN.format(epi=e, order=0) for e in (3, 6, 4))
+    names = [qkv, qkv, ATTN, res, res, ffn1, ffn1, res, res, qkv, qkv, ATTN, res, res]
+    assert P.dispatch_classes(names) == [
+        "qkv", "qkv", "attn", "oproj", "oproj", "ffn1", "ffn1", "ffn2", "ffn2",
+        "qkv", "qkv", "attn", "oproj", "oproj"]
+
+
 def _counter_csv(path, counter, rows):
     with open(path, "w", newline="") as fh:
         w = csv.writer(fh)
