@@ -343,9 +343,9 @@ hipError_t launch_mid(const uint16_t* X, const uint16_t* W, const float* bias, c
 // the stream of W over more CUs; once there is more than one per CU the
 // shared operand traffic costs more than it saves.  Measured (us per layer,
 // K = 3072, N = 768; 32x64 / 64x64 / 64x128 / 128x128 persistent tiles):
-//   M = 24    8.4 / 10.7 / 16.4 / 25.5     M = 512   9.6 / 11.9 / 20.3 / 27.2
-//   M = 1024  19.5 / 13.2 / 22.1 / 35.1    M = 2080  38.3 / 28.8 / 25.3 / 33.7
-//   M = 4096  58.9 / 48.6 / 47.5 / 34.3.
+//   M = 24    7.8 / 9.9 / 15.7 / 24.2      M = 512   8.1 / 10.1 / 16.1 / 24.9
+//   M = 1024  14.4 / 11.5 / 21.0 / 33.0    M = 2080  30.2 / 26.8 / 23.4 / 32.0
+//   M = 4096  47.8 / 45.3 / 45.0 / 31.7.
 static RingTile ring_tile(int64_t M, int N, int n_cus) {
   auto fits = [&](int bm, int bn) { return (M + bm - 1) / bm * (N / bn) <= n_cus; };
   if (fits(32, 64)) return RING_32x64;

@@ -99,8 +99,9 @@ __device__ __forceinline__ void ln_store(float (&v)[C][8], const float (&ga)[C][
 // Bound by HBM (a byte out per byte gathered); before, one wave took a row:
 // a third of its lanes idle at d = 768, gamma and beta loaded per row, and
 // twelve LDS shuffles in two chains.  2000 texts of ~54 tokens, us per call
-// (20 to 50 of them the host's), one row per wave / this / with STREAM_OUT: d = 768 139.7 / 109.7 / 86.9, 384 97 / 69 / 68, 1024 131 / 117 /
-// 112, 128 92 / 50 / 48.
+// (20 to 50 of them the host's), one row per wave / this / with STREAM_OUT:
+// d = 768 139.7 / 109.7 / 86.9, 384 97 / 69 / 68, 1024 131 / 117 / 112, 128
+// 92 / 50 / 48.
 template <int LPR, int C, bool STREAM_OUT>
 __global__ __launch_bounds__(256) void embed_ln_kernel(
     const int32_t* __restrict__ tokens, const RowBlock* __restrict__ items, int rows,
