@@ -367,10 +367,10 @@ hipError_t resolve_cus(int* n_cus) {
 // Which family a launch takes: beyond the small chunks 256 x 256 or 192 x 256
 // tiles (one workgroup per CU) or 128 x 128 tiles (two), by the cost of their
 // rounds.  The unit is a full round of 128-wide tiles.  Those fill the chip by
-// halves of a round and end about 0.05 late; a round of 256-row tiles does
+// halves of a round and end about 0.07 late; a round of 256-row tiles does
 // twice the work in 1.4 + 230 / (K + 350) units (the less, the more main loop
 // there is per epilogue: 1.45 at K = 4096, at most 1.84, where stores bound
-// both), and one of 192-row tiles three quarters of that in 0.82 of the time
+// both), and one of 192-row tiles three quarters of that in 0.84 of the time
 // (fewer MFMAs per operand byte), but a begun round costs a whole one, and
 // the first has 50 / K units of copies with no main loop to hide behind.
 // Fitted to 1,814 launches of N = 256 .. 4096, K = 64 .. 4096, M = 2500 ..
@@ -402,14 +402,14 @@ static Choice linear_family(int64_t M, int N, int K, int n_cus) {
   auto rounds = [&](int64_t bm, int columns) {
     return (double)(((M + bm - 1) / bm * columns + n_cus - 1) / n_cus);
   };
-  auto mid = [&](int columns) { return 0.5 * rounds(128, columns) + 0.05; };
+  auto mid = [&](int columns) { return 0.5 * rounds(128, columns) + 0.07; };
   const double wide = std::min(1.4 + 230.0 / (K + 350), 1.84), start = 50.0 / K;
   const double c256 = start + wide * rounds(256, N / 256);
   if (N % 256 != 0) {
     const bool split = N > 512 && c256 + mid(1) + 0.45 < mid(N / 128);
     return split ? Choice{FAMILY_WIDE_AND_MID, 256} : Choice{FAMILY_MID, 128};
   }
-  const double c128 = mid(N / 128), c192 = start + 0.82 * wide * rounds(192, N / 256);
+  const double c128 = mid(N / 128), c192 = start + 0.84 * wide * rounds(192, N / 256);
   if (c192 < c256 && c192 < c128) return {FAMILY_WIDE, 192};
   return c256 <= c128 ? Choice{FAMILY_WIDE, 256} : Choice{FAMILY_MID, 128};
 }
