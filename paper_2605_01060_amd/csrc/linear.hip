@@ -38,13 +38,10 @@
 // instruction) while stage k+1 runs on the MFMA units; one wait and one
 // barrier per stage.  An LDS row holds 64 bf16 of one X or W row as eight
 // 16-byte chunks; the logical chunk c of row r is stored at position
-// c ^ (r & 7) ^ ((r >> 3) & 1).  A fragment read takes four logical chunks
-// from 16 consecutive rows, 16 lanes a chunk; any 8 aligned rows fall on 8 different 16-byte
-// slots of a 128-byte window and any 16 aligned rows on 16 different slots
-// of a 256-byte window, so the reads are free of bank conflicts whether the
-// LDS serves a 16-byte read 8 lanes at a time over 32 banks or 16 lanes at
-// a time over 64 banks.  A copy instruction writes 64 consecutive slots, so
-// each lane fetches the logical chunk that belongs in its slot.
+// c ^ (r & 7), which leaves a fragment read (four logical chunks from 16
+// consecutive rows, 16 lanes a chunk) free of bank conflicts.  A copy
+// instruction writes 64 consecutive slots, so each lane fetches the logical
+// chunk that belongs in its slot.
 //
 // Occupancy.  Two workgroups per CU (64 + 4 KB of LDS each), 2 waves per
 // SIMD.
@@ -105,11 +102,11 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
 
   // Lane l of wave w, copy j, fills LDS slot p = (j*NWAVES + w)*64 + l of a
   // tile: row p / 8, stored chunk l % 8.  Its logical chunk
-  // (l & 7) ^ (l >> 3) ^ (w & 1) is the same for every j; its rows are
-  // NWAVES * 8 apart.
+  // (l & 7) ^ (l >> 3) is the same for every j; its rows are NWAVES * 8
+  // apart.
   constexpr int DSTEP = NWAVES * RPC;
   const int drow = wave * RPC + lane / CPR;
-  const int dch = copy_chunk<CPR>(lane, wave);
+  const int dch = copy_chunk16(lane);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * 64 * 16);
   constexpr uint32_t STAGE_BYTES = SSTAGE * 16;
   constexpr uint32_t COPY_BYTES = NWAVES * 64 * 16;
@@ -182,10 +179,10 @@ void linear_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restri
     const u32x4* sw = sx + BM * CPR;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
-      fa[ks][i] = __builtin_bit_cast(bf16x8, sw[swz<CPR>(wn0 + i * 16 + l16, ks * 4 + lq)]);
+      fa[ks][i] = __builtin_bit_cast(bf16x8, sw[swz16(wn0 + i * 16 + l16, ks * 4 + lq)]);
 #pragma unroll
     for (int j = 0; j < TJ; ++j)
-      fb[ks][j] = __builtin_bit_cast(bf16x8, sx[swz<CPR>(wm0 + j * 16 + l16, ks * 4 + lq)]);
+      fb[ks][j] = __builtin_bit_cast(bf16x8, sx[swz16(wm0 + j * 16 + l16, ks * 4 + lq)]);
   };
   int cur_buf = 0;
   int tpar = 0;
@@ -368,28 +365,28 @@ hipError_t resolve_cus(int* n_cus) {
 // tiles (one workgroup per CU) or 128 x 128 tiles (two), by the cost of their
 // rounds.  The unit is a full round of 128-wide tiles.  Those fill the chip by
 // halves of a round and end about 0.07 late; a round of 256-row tiles does
-// twice the work in 1.4 + 230 / (K + 350) units (the less, the more main loop
-// there is per epilogue: 1.45 at K = 4096, at most 1.84, where stores bound
-// both), and one of 192-row tiles three quarters of that in 0.84 of the time
-// (fewer MFMAs per operand byte), but a begun round costs a whole one, and
-// the first has 50 / K units of copies with no main loop to hide behind.
-// Fitted to 1,814 launches of N = 256 .. 4096, K = 64 .. 4096, M = 2500 ..
-// 262,144 timed under each family: the mean one takes 0.2 % longer than under
-// its best, the worst 13 %.  Measured (us, 128 / 192 / 256 rows):
-//   N = 2304, K = 768   M = 6144 28.0 / 37.7 / 24.2    8192 35.6 / 38.5 / 44.0
-//                       10,000 42.5 / 40.7 / 44.7      13,579 56.8 / 56.7 / 48.8
-//   N = 768, K = 3072   M = 8192 43.4 / 57.7 / 65.4    13,579 79.5 / 64.2 / 67.1
-//                       17,000 87.6 / 120 / 72.2       262,144 1,301 / 1,149 / 1,033
-//   N = 768, K = 256    M = 8192 8.0 / 10.2 / 11.7     262,144 153 / 146 / 133
-//   N = 2304, K = 64    M = 13,579 17.2 / 20.6 / 19.5  262,144 243 / 243 / 229.
+// twice the work in 1.4 + 240 / (K + 400) units (the less, the more main loop
+// there is per epilogue: 1.45 at K = 4096, at most 1.85, where stores bound
+// both), the first 50 / K later (copies with no main loop to hide behind), and
+// one of 192-row tiles three quarters of that in 0.834 of the time (fewer
+// MFMAs per operand byte), but a begun round costs a whole one.  Fitted to
+// 1,814 launches of N = 256 .. 4096, K = 64 .. 4096, M = 2500 .. 262,144 timed
+// under each family: the mean one takes 0.2 % longer than under its best, the
+// worst 8 %.  Measured (us, 128 / 192 / 256 rows):
+//   N = 2304, K = 768   M = 6144 28.2 / 35.5 / 23.9    8192 34.5 / 36.6 / 43.4
+//                       10,000 42.3 / 39.2 / 44.6      13,579 56.0 / 56.0 / 49.8
+//   N = 768, K = 3072   M = 8192 44.7 / 52.0 / 64.3    13,579 79.6 / 61.2 / 66.8
+//                       17,000 89.7 / 114 / 77.5       262,144 1,299 / 1,096 / 1,026
+//   N = 768, K = 256    M = 8192 7.9 / 9.6 / 11.4      262,144 149 / 140 / 131
+//   N = 2304, K = 64    M = 13,579 16.9 / 19.8 / 19.1  262,144 235 / 235 / 226.
 // An odd last 128 features take 128-wide tiles in a launch of their own, which
-// reads X once more and costs 0.45 units beside its rounds.  1,058 launches of
-// N = 384 .. 2432 are 0.1 % off their best in the mean (8 % at worst); all on
-// 128-wide tiles they are 1.4 % (47 %).  Measured (us, 128 / 128 and 256): N =
-// 1152, K = 64 M = 140,000 67.2 / 71.4, K = 3072 55,000 406 / 382; N = 640, K =
-// 3072 20,781 97.2 / 117, 55,000 255 / 244.  With one column of 256-wide tiles
-// before them (N = 384) it never paid: K = 768 M = 262,144 201 / 212, K = 1536
-// 100,000 151 / 179.
+// reads X once more and costs 0.7 units beside its rounds.  1,058 launches of
+// N = 384 .. 2432 are 0.2 % off their best in the mean (8 % at worst); all on
+// 128-wide tiles they are 1.5 % (49 %).  Measured (us, 128 / 128 and 256): N =
+// 1152, K = 64 M = 140,000 67.4 / 70.7, K = 3072 55,000 417 / 386; N = 640, K =
+// 3072 20,781 89.2 / 109, 75,000 320 / 363; N = 896, K = 768 100,000 184 / 182.
+// With one column of 256-wide tiles before them (N = 384) it never paid: K =
+// 768 M = 262,144 199 / 213, K = 1536 100,000 150 / 177.
 enum Family { FAMILY_RING, FAMILY_MID, FAMILY_WIDE, FAMILY_WIDE_AND_MID };
 struct Choice {
   Family family;
@@ -403,13 +400,13 @@ static Choice linear_family(int64_t M, int N, int K, int n_cus) {
     return (double)(((M + bm - 1) / bm * columns + n_cus - 1) / n_cus);
   };
   auto mid = [&](int columns) { return 0.5 * rounds(128, columns) + 0.07; };
-  const double wide = std::min(1.4 + 230.0 / (K + 350), 1.84), start = 50.0 / K;
-  const double c256 = start + wide * rounds(256, N / 256);
+  const double wide = std::min(1.4 + 240.0 / (K + 400), 1.85);
+  const double c256 = 50.0 / K + wide * rounds(256, N / 256);
   if (N % 256 != 0) {
-    const bool split = N > 512 && c256 + mid(1) + 0.45 < mid(N / 128);
+    const bool split = N > 512 && c256 + mid(1) + 0.7 < mid(N / 128);
     return split ? Choice{FAMILY_WIDE_AND_MID, 256} : Choice{FAMILY_MID, 128};
   }
-  const double c128 = mid(N / 128), c192 = start + 0.84 * wide * rounds(192, N / 256);
+  const double c128 = mid(N / 128), c192 = 0.834 * wide * rounds(192, N / 256);
   if (c192 < c256 && c192 < c128) return {FAMILY_WIDE, 192};
   return c256 <= c128 ? Choice{FAMILY_WIDE, 256} : Choice{FAMILY_MID, 128};
 }

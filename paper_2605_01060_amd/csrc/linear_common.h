@@ -186,7 +186,7 @@ __device__ __forceinline__ void store_tile(const Acc (&acc)[TI][TJ], Slot slot16
       for (int it = 0; it < 4; ++it) {
         const int m = min(mw + j * 32 + it * 8 + cr, M - 1);
         rv[p][it] = __builtin_nontemporal_load(
-            reinterpret_cast<const u32x4*>(R + (size_t)m * N + nw + ip * 64 + 8 * cp));
+            reinterpret_cast<const u32x4*>(R + (size_t)m * N + (nw + ip * 64 + 8 * cp)));
       }
     }
   }
@@ -254,7 +254,7 @@ __device__ __forceinline__ void store_tile(const Acc (&acc)[TI][TJ], Slot slot16
       const int m = mw + j * 32 + it * 8 + cr;
       if (m < M)
         __builtin_nontemporal_store(
-            ov[it], reinterpret_cast<u32x4*>(Y + (size_t)m * N + nw + ip * 64 + 8 * cp));
+            ov[it], reinterpret_cast<u32x4*>(Y + (size_t)m * N + (nw + ip * 64 + 8 * cp)));
     }
   }
 }

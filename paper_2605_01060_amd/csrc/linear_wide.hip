@@ -25,18 +25,23 @@
 //
 // The copy stream runs on across tile boundaries.  Only the phase-1 rows of
 // the next tile's second stage are held back: their LDS and 16 KB (24 KB)
-// beside the stages are the waves' epilogue regions.  The accumulators see the same K order as every other tile shape.
+// beside the stages are the waves' epilogue regions.  The accumulators see the
+// same K order as every other tile shape.
 //
 // Measured against the loop of one-stage tolerance on 32x32x16 MFMAs that it
-// replaces (M = 262,144, us): QKV 898 -> 828, FFN2 1,132 -> 1,061, FFN1
-// 1,390 -> 1,309, O-projection 375 -> 364.
+// replaces (M = 262,144, us, normal data): QKV 907 -> 849, FFN2 1,151 ->
+// 1,066, FFN1 1,436 -> 1,298, O-projection 391 -> 373.
 //
-// No instance may spill: a spilled address that a copy uses brings a wait for
-// every copy in flight into the K loop.  One register did so in FFN1, FFN2 and
-// the O-projection; without it (M = 262,144, us, on zeros / on normal data)
-// FFN1 1,083 -> 1,057 / 1,310 -> 1,309, FFN2 887 -> 842 / 1,079 -> 1,074,
-// O-projection 325 -> 318 / 377 -> 373: on normal data the power limit takes
-// most of it back.
+// Two things that the schedule needs, and what they measure:
+//   - No instance may spill: a spilled address that a copy uses brings a wait
+//     for every copy in flight into the K loop.  One register did so in FFN1,
+//     FFN2 and the O-projection; without it, on zeros, where power does not
+//     count, FFN1 1,083 -> 1,057, FFN2 887 -> 842, O-projection 325 -> 318,
+//     and at most 1 % on normal data: the power limit takes it back.
+//   - Fragment reads without bank conflicts (swz16).  With the swizzle of
+//     32-row reads 44 % of the LDS's busy cycles were conflicts, FFN2 of
+//     24,000 rows (N = 1024, K = 4096) took 180 us and not 169, QKV, FFN1 and
+//     FFN2 of 262,144 rows 1 to 1.5 % more.
 #include <algorithm>
 
 #include "linear_common.h"
@@ -119,12 +124,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
   // K stage.
   auto tile_addresses = [&](uint32_t p) {
     const int l = opaque_lane();
-    const uint32_t ch = (uint32_t)swz<8>(l & 15, l >> 4) * 16u + p * BUF;
+    const uint32_t ch = (uint32_t)swz16(l & 15, l >> 4) * 16u + p * BUF;
     aw = lds + (uint32_t)wn0 * 128u + ch;
     ax = lds + X0 + (uint32_t)(wave_m * R0) * 128u + ch;
     ax1 = lds + X1 + (uint32_t)(wave_m * R1) * 128u + ch;
     wo = __umul24((uint32_t)(wave * 8 + (l >> 3)), (uint32_t)K * 2u) +
-         (uint32_t)copy_chunk<8>(l, wave) * 16u;
+         (uint32_t)copy_chunk16(l) * 16u;
   };
   auto point = [&]() {
     int tm_, tn_;
@@ -137,7 +142,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
       const int lr = (q & 1) * 64 + wave * 8 + (l >> 3);
       const int row = q < 2 ? lr / R0 * (R0 + R1) + lr % R0 : lr / R1 * (R0 + R1) + R0 + lr % R1;
       xo[q] = __umul24((uint32_t)min(row, M - 1 - tm_ * BM), (uint32_t)K * 2u) +
-              (uint32_t)copy_chunk<8>(l, wave) * 16u;
+              (uint32_t)copy_chunk16(l) * 16u;
     }
   };
   // Copy c of the cursor's stage into parity p, skipped where `go` is 0:

@@ -8,22 +8,22 @@ from paper_2605_01060_amd import surge as S
 # (M, N, K), us with 128-wide, 192-row and 256-row tiles (for N not a multiple
 # of 256 the last 128 features are 128-wide in each)
 MEASURED = [
-    ((262_144, 768, 64), 85.1, 87.4, 81.5), ((262_144, 2304, 64), 243.4, 242.8, 229.0),
-    ((13_579, 2304, 64), 17.2, 20.6, 19.5), ((30_000, 1024, 64), 17.3, 20.4, 19.7),
-    ((262_144, 768, 256), 153.2, 145.6, 132.5), ((100_000, 2304, 256), 168.5, 161.6, 150.1),
-    ((262_144, 3072, 128), 410.2, 392.2, 369.2), ((100_000, 1024, 384), 101.3, 99.1, 97.5),
-    ((8192, 768, 256), 8.0, 10.2, 11.7), ((13_579, 512, 384), 9.8, 12.2, 14.3),
-    ((75_000, 256, 4096), 231.9, 183.4, 213.9), ((40_000, 512, 4096), 211.3, 172.5, 188.3),
-    ((6144, 2304, 768), 28.0, 37.7, 24.2), ((8192, 2304, 768), 35.6, 38.5, 44.0),
-    ((10_000, 2304, 768), 42.5, 40.7, 44.7), ((13_579, 2304, 768), 56.8, 56.7, 48.8),
-    ((8192, 768, 3072), 43.4, 57.7, 65.4), ((13_579, 768, 3072), 79.5, 64.2, 67.1),
-    ((17_000, 768, 3072), 87.6, 120.0, 72.2), ((262_144, 768, 3072), 1300.8, 1148.5, 1032.9),
+    ((262_144, 768, 64), 85.2, 85.0, 79.9), ((262_144, 2304, 64), 234.9, 234.6, 225.7),
+    ((13_579, 2304, 64), 16.9, 19.8, 19.1), ((30_000, 1024, 64), 17.2, 19.7, 19.3),
+    ((262_144, 768, 256), 149.3, 140.4, 131.2), ((100_000, 2304, 256), 167.4, 153.7, 148.2),
+    ((262_144, 3072, 128), 401.7, 375.7, 356.5), ((11_500, 768, 256), 11.2, 9.7, 11.4),
+    ((8192, 768, 256), 7.9, 9.6, 11.4), ((13_579, 512, 384), 9.7, 11.3, 13.8),
+    ((75_000, 256, 4096), 232.0, 177.0, 213.6), ((40_000, 512, 4096), 209.4, 163.7, 189.1),
+    ((6144, 2304, 768), 28.2, 35.5, 23.9), ((8192, 2304, 768), 34.5, 36.6, 43.4),
+    ((10_000, 2304, 768), 42.3, 39.2, 44.6), ((13_579, 2304, 768), 56.0, 56.0, 49.8),
+    ((8192, 768, 3072), 44.7, 52.0, 64.3), ((13_579, 768, 3072), 79.6, 61.2, 66.8),
+    ((17_000, 768, 3072), 89.7, 114.1, 77.5), ((262_144, 768, 3072), 1298.8, 1095.5, 1025.7),
     # an odd number of 128 features
-    ((140_000, 1152, 64), 67.2, 75.7, 71.4), ((55_000, 1152, 384), 68.1, 69.3, 69.8),
-    ((55_000, 1152, 3072), 406.1, 398.4, 381.7), ((75_000, 1152, 3072), 568.4, 577.3, 525.0),
-    ((20_781, 640, 3072), 97.2, 112.2, 117.4), ((55_000, 640, 3072), 254.9, 272.3, 244.3),
-    ((55_000, 896, 768), 84.3, 91.9, 87.9), ((75_000, 640, 3072), 333.6, 400.0, 372.8),
-    ((262_144, 384, 768), 201.2, 230.1, 212.0), ((100_000, 384, 1536), 151.4, 194.1, 178.5),
+    ((140_000, 1152, 64), 67.4, 72.0, 70.7), ((55_000, 1152, 384), 65.2, 67.1, 69.3),
+    ((55_000, 1152, 3072), 417.4, 390.5, 386.3), ((75_000, 1152, 3072), 565.0, 553.0, 521.5),
+    ((20_781, 640, 3072), 89.2, 102.3, 109.1), ((75_000, 640, 3072), 320.2, 378.6, 363.1),
+    ((55_000, 896, 768), 83.4, 88.2, 87.6), ((100_000, 896, 768), 183.5, 189.6, 181.5),
+    ((262_144, 384, 768), 198.5, 229.5, 212.8), ((100_000, 384, 1536), 149.8, 192.0, 177.2),
 ]
 
 
