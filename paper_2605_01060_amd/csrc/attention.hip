@@ -24,8 +24,10 @@
 // bytes (one 64-dimensional head, or a pair of 32-dimensional heads as
 // below).  Q, K and V blocks move from global memory to LDS with
 // direct copies that read whole rows (8 lanes per 128-byte row), stored in
-// the conflict-free chunk swizzle; the next K/V block is copied into the
-// second LDS buffer while the current one is on the MFMA units.  The output
+// the chunk swizzle that frees the Q and K reads of bank conflicts (not the
+// transposing V reads: 31 % of the LDS's cycles, which are 16 % of the
+// time); the next K/V block is copied into the second LDS buffer while the
+// current one is on the MFMA units.  The output
 // block is staged in LDS and written back as whole rows too.  (Reading the
 // MFMA operands straight from global memory would touch 32 rows per
 // instruction for 32 bytes each, which stalls the address path.)

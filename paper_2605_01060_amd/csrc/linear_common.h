@@ -112,10 +112,9 @@ __device__ __forceinline__ void tile_coords(int b, int n_tiles, int tiles_n, int
 }
 
 // Epilogue region layout: 32 rows x 64 bf16, a row as 16 8-byte units;
-// unit u of row r sits at u ^ rsw(r).  The 32 rows that one 8-byte access
-// of a wave spans (one unit each) land on distinct banks under either LDS
-// bank geometry, and an aligned 16-byte pair {2k, 2k+1} stays together
-// (halves swapped when rsw(r) is odd).
+// unit u of row r sits at u ^ rsw(r).  The 16 rows of two units that half a
+// wave's 8-byte access spans land on distinct banks, and an aligned 16-byte
+// pair {2k, 2k+1} stays together (halves swapped when rsw(r) is odd).
 __device__ __forceinline__ int rsw(int r) { return (r & 15) ^ ((r >> 4) & 1); }
 
 // Accumulators.  The large tiles multiply with 16x16x32 bf16 MFMAs, A =
